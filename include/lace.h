@@ -192,7 +192,7 @@ int lace_apply_exchange_virtual(lace_plan* plan, int cell, const void* psi_g,
  * Reading: the unitary U that minimizes ||psi_new U - psi_old||_F (the
  * orthogonal Procrustes problem) is the polar factor of
  * A = psi_new^H psi_old; psi_out = psi_new U spans the space of psi_new.
- * U is computed on the device by 30 Newton-Schulz steps
+ * U is computed on the device by at most 30 Newton-Schulz steps
  * X <- X (3 I - X^H X) / 2 from X_0 = A / b, b^2 >= the largest eigenvalue
  * of A^H A (Gershgorin); singular values of A below ~1e-4 of the largest
  * are not resolved (resid then stays large).

@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liblace.so")
 OBJDIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["lace_api.hip", "fft_kernels.hip", "dense_kernels.hip",
+SOURCES = ["lace_api.hip", "fft_kernels.hip", "dense_kernels.hip", "polar_kernels.hip",
            "scdm_kernels.hip", "screen_kernels.hip"]
 
 HIPCC_FLAGS = [

@@ -167,13 +167,15 @@ hipError_t launch_trinv_adj(const void* L, int n, void* Z, hipStream_t st);
 hipError_t launch_trace_re(const void* M, int n, double factor, double* out,
                            hipStream_t st);
 
-// Polar-iteration helpers, n x n complex128 row-major.  elem: 0 conj,
-// 1 scale by *s, 2 (3 I - in) / 2, 3 transpose (out distinct from in).
-// norm: 0 Gershgorin scale 1 / sqrt(max row sum |B|), 1 ||B - I||_F / sqrt n.
-hipError_t launch_polar_elem(int mode, const void* in, int n, const double* s,
-                             void* out, hipStream_t st);
-hipError_t launch_polar_norm(int mode, const void* B, int n, double* out,
-                             hipStream_t st);
+// U (n x n complex128, row-major) <- unitary polar factor of A, given
+// Y0 = A^T row-major (its conjugate when conj_in).  ya, yb, b: n x n
+// complex128 scratch (Y0 may be ya); state: polar_state_bytes() of scratch;
+// resid (device, may be null) <- ||U^H U - I||_F / sqrt n.  U may not
+// overlap the others.
+hipError_t launch_polar(const void* Y0, bool conj_in, int n, void* ya, void* yb,
+                        void* b, void* state, void* U, double* resid,
+                        hipStream_t st);
+int64_t polar_state_bytes();
 
 // ---- screening decision and batch schedule on the device ----
 // Kept pairs of Eq. (6) from S (n x n, device): pairs (2 int32 each) column
@@ -230,3 +232,21 @@ hipError_t launch_scdm(bool fp64, bool real, const void* psi, int n_orb,
     if (lace_resolve_err_ != hipSuccess) return lace_resolve_err_; \
     hipLaunchKernelGGL(K, __VA_ARGS__);                            \
   } while (0)
+
+// The host layer also builds as plain C++ without the kernels (its thread
+// and address checks): launchers without a stand-in of their own there
+// write the whole extent of their outputs.
+#if !defined(__HIP__)
+#include <cstring>
+namespace lace {
+inline int64_t polar_state_bytes() { return 512; }
+inline hipError_t launch_polar(const void*, bool, int n, void* ya, void* yb,
+                               void* b, void* state, void* U, double* resid,
+                               hipStream_t) {
+  for (void* p : {ya, yb, b, U}) std::memset(p, 0x3c, 16 * (size_t)n * n);
+  std::memset(state, 0, (size_t)polar_state_bytes());
+  if (resid) *resid = 0.0;
+  return hipSuccess;
+}
+}  // namespace lace
+#endif

@@ -851,43 +851,15 @@ int lace_apply_exchange(lace_plan* p, int cell, const void* psi_g, int n_orb,
   return hip_status(e);
 }
 
-// Newton-Schulz steps of the polar factor; quadratic near convergence and
-// growing the smallest singular value by 3/2 per step before that, so 30
-// steps resolve singular values down to ~1e-4 of the largest.
-static constexpr int kAlignSteps = 30;
-
-// Polar factor U of an n x n complex matrix A, given Y_0 = A^T (row-major)
-// in the workspace's `a` block: X_0 = A s with s from a Gershgorin bound,
-// then X <- X (3 I - X^H X) / 2, kept transposed (Y = X^T).  Leaves U
+// Polar factor U of an n x n complex matrix A, given Y_0 = A^T (row-major,
+// its conjugate when conj_in) in the workspace's `a` block.  Leaves U
 // (row-major) in the `mw` block; resid (device, may be NULL) gets
-// ||U^H U - I||_F / sqrt(n).
-static hipError_t enqueue_polar(const Layout& L, void* ws, int n, double* resid,
-                                hipStream_t st) {
-  void* part = at(ws, L.part);
-  const int64_t pb = (int64_t)(L.mw - L.part);
-  void* g = at(ws, L.mw);     // C, finally U
-  void* y0 = at(ws, L.a);     // Y, ping
-  void* y1 = at(ws, L.u);     // pong
-  void* b = at(ws, L.z);      // X^H X
-  double* sc = reinterpret_cast<double*>(at(ws, L.s));
-  hipError_t e = launch_gemm_ip_c128(y0, n, n, y0, n, n, n, 1.0, b, part, pb, st);
-  if (e == hipSuccess) e = launch_polar_norm(0, b, n, sc, st);
-  if (e == hipSuccess) e = launch_polar_elem(1, y0, n, sc, y1, st);
-  void* cur = y1;
-  void* nxt = y0;
-  for (int it = 0; it < kAlignSteps && e == hipSuccess; ++it) {
-    // X <- X C, C = (3 I - X^H X) / 2: Y'[b][a] = sum_k Y[k][a] C[k][b]
-    e = launch_gemm_ip_c128(cur, n, n, cur, n, n, n, 1.0, b, part, pb, st);
-    if (e == hipSuccess) e = launch_polar_elem(2, b, n, nullptr, g, st);
-    if (e == hipSuccess) e = launch_gemm_tall(cur, n, n, n, g, n, nxt, n, st);
-    std::swap(cur, nxt);
-  }
-  if (e == hipSuccess && resid) {
-    e = launch_gemm_ip_c128(cur, n, n, cur, n, n, n, 1.0, b, part, pb, st);
-    if (e == hipSuccess) e = launch_polar_norm(1, b, n, resid, st);
-  }
-  if (e == hipSuccess) e = launch_polar_elem(3, cur, n, nullptr, g, st);  // U = Y^T
-  return e;
+// ||U^H U - I||_F / sqrt(n).  The iteration's state goes to the SCDM
+// scratch, free by then.
+static hipError_t enqueue_polar(const Layout& L, void* ws, int n, bool conj_in,
+                                double* resid, hipStream_t st) {
+  return launch_polar(at(ws, L.a), conj_in, n, at(ws, L.a), at(ws, L.u),
+                      at(ws, L.z), at(ws, L.scdm), at(ws, L.mw), resid, st);
 }
 
 int lace_align(lace_plan* p, int cell, const void* psi_new, const void* psi_old,
@@ -905,10 +877,9 @@ int lace_align(lace_plan* p, int cell, const void* psi_new, const void* psi_old,
   // G[x][y] = <psi_old_x | psi_new_y> = conj(A[y][x]), A = psi_new^H psi_old,
   // so Y_0 = A^T = conj(G)
   hipError_t e = launch_gemm_ip_c128(psi_old, c.n_pw, n, psi_new, c.n_pw, n,
-                                     c.n_pw, 1.0, at(ws, L.mw), at(ws, L.part),
+                                     c.n_pw, 1.0, at(ws, L.a), at(ws, L.part),
                                      (int64_t)(L.mw - L.part), st);
-  if (e == hipSuccess) e = launch_polar_elem(0, at(ws, L.mw), n, nullptr, at(ws, L.a), st);
-  if (e == hipSuccess) e = enqueue_polar(L, ws, n, resid, st);
+  if (e == hipSuccess) e = enqueue_polar(L, ws, n, true, resid, st);
   // psi_out_b = sum_a psi_new_a U[a][b]
   if (e == hipSuccess)
     e = launch_gemm_tall(psi_new, c.n_pw, c.n_pw, n, at(ws, L.mw), n, psi_out,
@@ -933,7 +904,7 @@ int lace_scdm(lace_plan* p, int cell, const void* psi_g, int n_orb,
     e = launch_scdm(p->fp64, p->gamma, at(ws, L.psi), n_orb, c.ng,
                     reinterpret_cast<double*>(at(ws, L.dens)), at(ws, L.scdm),
                     pts, at(ws, L.a), st);
-  if (e == hipSuccess) e = enqueue_polar(L, ws, n_orb, resid, st);
+  if (e == hipSuccess) e = enqueue_polar(L, ws, n_orb, false, resid, st);
   // phi_k = sum_n psi_n U[n][k]
   if (e == hipSuccess)
     e = launch_gemm_tall(psi_g, c.n_pw, c.n_pw, n_orb, at(ws, L.mw), n_orb,
