@@ -215,11 +215,13 @@ int64_t sched_slot_bound(int n_orb);
 // SCDM point selection on the workspace orbital grids (complex or real,
 // FP32 or FP64): n_orb greedy picks of column-pivoted QR of Psi^H into
 // points (device int32), then Y[k][n] = conj(psi_n(points[k])) (n_orb x n_orb
-// complex128 row-major).  d: ng doubles; scratch: scdm_scratch_bytes.
+// complex128 row-major).  d: ng doubles; scratch: scdm_scratch_bytes; buf:
+// buf_bytes of further scratch (the W grids' region), apart from psi.
 int64_t scdm_scratch_bytes(int n_orb);
 hipError_t launch_scdm(bool fp64, bool real, const void* psi, int n_orb,
-                       int64_t ng, double* d, void* scratch, int32_t* points,
-                       void* Y, hipStream_t st);
+                       int64_t ng, double* d, void* scratch, void* buf,
+                       int64_t buf_bytes, int32_t* points, void* Y,
+                       hipStream_t st);
 
 }  // namespace lace
 
@@ -246,6 +248,17 @@ inline hipError_t launch_polar(const void*, bool, int n, void* ya, void* yb,
   for (void* p : {ya, yb, b, U}) std::memset(p, 0x3c, 16 * (size_t)n * n);
   std::memset(state, 0, (size_t)polar_state_bytes());
   if (resid) *resid = 0.0;
+  return hipSuccess;
+}
+inline hipError_t launch_scdm(bool, bool, const void* psi, int n_orb, int64_t ng,
+                              double* d, void* scratch, void* buf,
+                              int64_t buf_bytes, int32_t* points, void* Y,
+                              hipStream_t) {
+  std::memset(d, static_cast<const char*>(psi)[0] & 1, sizeof(double) * (size_t)ng);
+  std::memset(scratch, 0x3c, (size_t)scdm_scratch_bytes(n_orb));
+  std::memset(buf, 0x3c, (size_t)buf_bytes);
+  for (int k = 0; k < n_orb; ++k) points[k] = k;
+  std::memset(Y, 0x3c, 16 * (size_t)n_orb * n_orb);
   return hipSuccess;
 }
 }  // namespace lace

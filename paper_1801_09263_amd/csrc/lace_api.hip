@@ -903,7 +903,7 @@ int lace_scdm(lace_plan* p, int cell, const void* psi_g, int n_orb,
   if (e == hipSuccess)
     e = launch_scdm(p->fp64, p->gamma, at(ws, L.psi), n_orb, c.ng,
                     reinterpret_cast<double*>(at(ws, L.dens)), at(ws, L.scdm),
-                    pts, at(ws, L.a), st);
+                    at(ws, L.w), (int64_t)(L.tmp - L.w), pts, at(ws, L.a), st);
   if (e == hipSuccess) e = enqueue_polar(L, ws, n_orb, false, resid, st);
   // phi_k = sum_n psi_n U[n][k]
   if (e == hipSuccess)
