@@ -378,6 +378,126 @@ static hipError_t launch_splitk_reduce(const double* part, int64_t nel,
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------------
+// Narrow inner products, nb <= 32: part[z][a][b] as k_gemm_ip<0> writes it.
+// A few functions against all orbitals (a solver's block), or a small cell:
+// the 64 x 64 tile above multiplies mostly padding there (nb = 6: 10 of 11
+// products), and the work is bound by reading A once.  A wave takes 32 rows
+// a (two MFMA tiles) x 16 NBT columns b and reads its operands straight
+// from memory, four consecutive k per lane (64 bytes; any order of k will
+// do), the next block's loads issued before this block's MFMAs.  The four
+// waves of a workgroup take blocks of 16 k in turn and add their tiles in
+// wave order in LDS, so the partials stay few.
+// 131 orbitals x 6 functions x 167,037: the whole application 488 -> 212 us
+// (this, its reduction and the tall product below; xi, 350 MB, is read twice:
+// 3.3 TB/s).
+// ------------------------------------------------------------------
+constexpr int NR_A = 32;        // rows a of a workgroup
+constexpr int NR_B = 32;        // the most columns b
+constexpr int NR_K = 64;        // k of one round of a workgroup
+template <int NBT>
+__global__ __launch_bounds__(256) void k_ip_narrow(const double2* A, int64_t lda,
+                                                   int na, const double2* B,
+                                                   int64_t ldb, int nb,
+                                                   int64_t K, int64_t kchunk,
+                                                   double* part) {
+  constexpr int NACC = 2 * NBT * 8;   // doubles per lane
+  __shared__ double red[3][64][NACC + 1];
+  const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
+  const int l16 = lane % 16, g = lane / 16;
+  const int a0 = blockIdx.x * NR_A;
+  const int64_t kb = blockIdx.y * kchunk;
+  const int64_t ke = kb + kchunk < K ? kb + kchunk : K;
+  // rows past the end repeat the last one; their results are not stored
+  const double2* pa[2];
+  const double2* pb[NBT];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+    pa[p] = A + (int64_t)min(a0 + 16 * p + l16, na - 1) * lda;
+#pragma unroll
+  for (int q = 0; q < NBT; ++q) pb[q] = B + (int64_t)min(16 * q + l16, nb - 1) * ldb;
+  d4 re[2][NBT], im[2][NBT];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int q = 0; q < NBT; ++q) {
+      re[p][q] = d4{0, 0, 0, 0};
+      im[p][q] = d4{0, 0, 0, 0};
+    }
+  double2 xa[2][4], xb[NBT][4];
+  auto fetch = [&](int64_t k0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int64_t k = k0 + 4 * g + s;
+      const int64_t kc = k < ke ? k : ke - 1;   // a valid entry, zeroed below
+#pragma unroll
+      for (int p = 0; p < 2; ++p) xa[p][s] = pa[p][kc];
+#pragma unroll
+      for (int q = 0; q < NBT; ++q) xb[q][s] = pb[q][kc];
+    }
+  };
+  int64_t k0 = kb + 16 * w;
+  if (k0 < ke) fetch(k0);
+  for (; k0 < ke; k0 += NR_K) {
+    double2 ya[2][4], yb[NBT][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool in = k0 + 4 * g + s < ke;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) ya[p][s] = xa[p][s];
+#pragma unroll
+      for (int q = 0; q < NBT; ++q)
+        yb[q][s] = make_double2(in ? xb[q][s].x : 0.0, in ? xb[q][s].y : 0.0);
+    }
+    if (k0 + NR_K < ke) fetch(k0 + NR_K);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < NBT; ++q) {
+          // conj(a) b = (ar br + ai bi) + i (ar bi - ai br)
+          re[p][q] = mfma(ya[p][s].x, yb[q][s].x, re[p][q]);
+          im[p][q] = mfma(ya[p][s].x, yb[q][s].y, im[p][q]);
+          re[p][q] = mfma(ya[p][s].y, yb[q][s].y, re[p][q]);
+          im[p][q] = mfma(-ya[p][s].y, yb[q][s].x, im[p][q]);
+        }
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int q = 0; q < NBT; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          red[w - 1][lane][(p * NBT + q) * 8 + e] = re[p][q][e];
+          red[w - 1][lane][(p * NBT + q) * 8 + 4 + e] = im[p][q][e];
+        }
+  }
+  __syncthreads();
+  if (w > 0) return;
+  double* out = part + (int64_t)blockIdx.y * na * nb * 2;
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int q = 0; q < NBT; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = (p * NBT + q) * 8 + e;
+        double r = re[p][q][e], c = im[p][q][e];
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+          r += red[v][lane][i];
+          c += red[v][lane][i + 4];
+        }
+        const int a = a0 + 16 * p + g + 4 * e, b = 16 * q + l16;
+        if (a < na && b < nb) {
+          out[2 * ((int64_t)a * nb + b)] = r;
+          out[2 * ((int64_t)a * nb + b) + 1] = c;
+        }
+      }
+}
+
 struct SplitPlan {
   int nsplit;
   int64_t kchunk;
@@ -401,8 +521,23 @@ static SplitPlan split_plan(int na, int nb, int64_t K) {
   return sp;
 }
 
+// The narrow form's split: about 1024 workgroups, whole rounds of k.
+static SplitPlan narrow_plan(int na, int64_t K) {
+  const int64_t tiles = (na + NR_A - 1) / NR_A;
+  const int64_t rounds = (K + NR_K - 1) / NR_K;
+  int64_t want = (1024 + tiles - 1) / tiles;
+  if (want > rounds) want = rounds;
+  if (want < 1) want = 1;
+  SplitPlan sp;
+  sp.kchunk = ((rounds + want - 1) / want) * NR_K;
+  sp.nsplit = (int)((K + sp.kchunk - 1) / sp.kchunk);
+  if (sp.nsplit < 1) sp.nsplit = 1;
+  return sp;
+}
+
 int64_t gemm_ip_part_bytes(int na, int nb, int64_t K, bool complex_out) {
-  const SplitPlan sp = split_plan(na, nb, K);
+  const SplitPlan sp =
+      complex_out && nb <= NR_B ? narrow_plan(na, K) : split_plan(na, nb, K);
   return (int64_t)sp.nsplit * na * nb * (complex_out ? 16 : 8);
 }
 
@@ -450,8 +585,30 @@ hipError_t launch_gemm_ip_c128(const void* A, int64_t lda, int na,
                                const void* B, int64_t ldb, int nb, int64_t K,
                                double scale, void* out, void* part,
                                int64_t part_bytes, hipStream_t st) {
-  return gemm_ip<0>(A, lda, na, B, ldb, nb, K, scale,
-                    static_cast<double*>(out), part, part_bytes, st);
+  if (nb > NR_B)
+    return gemm_ip<0>(A, lda, na, B, ldb, nb, K, scale,
+                      static_cast<double*>(out), part, part_bytes, st);
+  // up to 32 columns.  A whole application (64 x 64 tiles -> narrow): 64
+  // orbitals of 64^3 x 1 / 17 / 32 functions 80 / 84 / 88 -> 39 / 74 / 80 us,
+  // 131 of 96^3 x 6 / 16 / 32 488 / 491 / 502 -> 212 / 250 / 324 us, 256 of
+  // 120^3 x 4 / 32 683 / 700 -> 325 / 473 us; from 33 on the padding is less
+  // than half and the staged tiles read A and B less often.
+  const SplitPlan sp = narrow_plan(na, K);
+  if ((int64_t)sp.nsplit * na * nb * 16 > part_bytes) return hipErrorInvalidValue;
+  const dim3 grid((na + NR_A - 1) / NR_A, sp.nsplit);
+  const double2* a = static_cast<const double2*>(A);
+  const double2* b = static_cast<const double2*>(B);
+  double* p = static_cast<double*>(part);
+  if (nb <= 16)
+    LACE_LAUNCH(k_ip_narrow<1>, grid, dim3(256), 0, st, a, lda, na, b, ldb, nb, K,
+                sp.kchunk, p);
+  else
+    LACE_LAUNCH(k_ip_narrow<2>, grid, dim3(256), 0, st, a, lda, na, b, ldb, nb, K,
+                sp.kchunk, p);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  return launch_splitk_reduce(p, (int64_t)na * nb * 2, sp.nsplit, scale,
+                              static_cast<double*>(out), 0, st);
 }
 
 hipError_t launch_gemm_ip_abs(bool fp64, const void* A, int64_t lda, int na,
@@ -560,9 +717,89 @@ __global__ __launch_bounds__(256) void k_gemm_tall(const double2* X,
   }
 }
 
+// Narrow tall product, nb <= 32: bound by reading X once and writing Y.  A
+// wave takes 32 points m x 16 NBT columns b, D = Z^T X with the rows of D
+// along b, so that a store writes 16 consecutive points (256 bytes) of a
+// column; Z stays in the caches.  Every load of four k steps is issued
+// before their MFMAs; past the last k a valid entry is read and Z's zeroed.
+template <int NBT>
+__global__ __launch_bounds__(256) void k_tall_narrow(const double2* X, int64_t ldx,
+                                                     int64_t M, int nk,
+                                                     const double2* Z, int nb,
+                                                     double2* Y, int64_t ldy) {
+  const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
+  const int l16 = lane % 16, g = lane / 16;
+  const int64_t m0 = ((int64_t)blockIdx.x * 4 + w) * 32;
+  if (m0 >= M) return;
+  const double2* px[2];
+  const double2* pz[NBT];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) px[p] = X + (m0 + 16 * p + l16 < M ? m0 + 16 * p + l16 : M - 1);
+#pragma unroll
+  for (int q = 0; q < NBT; ++q) pz[q] = Z + min(16 * q + l16, nb - 1);
+  d4 re[NBT][2], im[NBT][2];
+#pragma unroll
+  for (int q = 0; q < NBT; ++q)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      re[q][p] = d4{0, 0, 0, 0};
+      im[q][p] = d4{0, 0, 0, 0};
+    }
+  for (int k0 = 0; k0 < nk; k0 += 16) {
+    double2 x[2][4], z[NBT][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = k0 + 4 * s + g, kc = min(k, nk - 1);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) x[p][s] = px[p][(int64_t)kc * ldx];
+#pragma unroll
+      for (int q = 0; q < NBT; ++q) z[q][s] = pz[q][(int64_t)kc * nb];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool in = k0 + 4 * s + g < nk;
+#pragma unroll
+      for (int q = 0; q < NBT; ++q) {
+        const double zr = in ? z[q][s].x : 0.0, zi = in ? z[q][s].y : 0.0;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          re[q][p] = mfma(zr, x[p][s].x, re[q][p]);
+          im[q][p] = mfma(zr, x[p][s].y, im[q][p]);
+          re[q][p] = mfma(-zi, x[p][s].y, re[q][p]);
+          im[q][p] = mfma(zi, x[p][s].x, im[q][p]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NBT; ++q)
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int b = 16 * q + g + 4 * e;
+        const int64_t m = m0 + 16 * p + l16;
+        if (b < nb && m < M) Y[(int64_t)b * ldy + m] = make_double2(re[q][p][e], im[q][p][e]);
+      }
+}
+
 hipError_t launch_gemm_tall(const void* X, int64_t ldx, int64_t M, int nk,
                             const void* Z, int nb, void* Y, int64_t ldy,
                             hipStream_t st) {
+  if (nb <= NR_B) {
+    const int64_t nblk = (M + 127) / 128;
+    if (nblk > INT32_MAX) return hipErrorInvalidValue;
+    const double2* x = static_cast<const double2*>(X);
+    const double2* z = static_cast<const double2*>(Z);
+    double2* y = static_cast<double2*>(Y);
+    if (nb <= 16)
+      LACE_LAUNCH(k_tall_narrow<1>, dim3((unsigned)nblk), dim3(256), 0, st, x, ldx, M,
+                  nk, z, nb, y, ldy);
+    else
+      LACE_LAUNCH(k_tall_narrow<2>, dim3((unsigned)nblk), dim3(256), 0, st, x, ldx, M,
+                  nk, z, nb, y, ldy);
+    return hipGetLastError();
+  }
   const int nbb = (nb + 63) / 64;
   const int64_t blocks = ((M + 63) / 64) * nbb;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
