@@ -180,31 +180,24 @@ __device__ inline bool kbit(const uint64_t* kb, int words, int a, int b) {
 
 // kb[a][b] = 1 for a != b with S[a][b] >= thr (S symmetric, ns x ns:
 // orbitals from ns on have no two-sided pairs); db bit a for S[a][a] >= thr.
-// s == nullptr: every pair of the first ns orbitals.  One thread per word.
-__global__ void k_sched_bits_s(const double* __restrict__ s, int n, int ns,
-                               int words, double thr, uint64_t* __restrict__ kb,
-                               uint64_t* __restrict__ db) {
-  const int64_t total = (int64_t)n * words;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
+// s == nullptr: every pair of the first ns orbitals.  One wave per word, a
+// lane per bit (coalesced rows of S; one thread per word took 13 to 34 us
+// for 32 to 77 orbitals, this 4); row n is the diagonal.
+__global__ __launch_bounds__(256) void k_sched_bits_s(
+    const double* __restrict__ s, int n, int ns, int words, double thr,
+    uint64_t* __restrict__ kb, uint64_t* __restrict__ db) {
+  const int64_t total = (int64_t)(n + 1) * words;
+  const int lane = threadIdx.x & 63;
+  for (int64_t t = blockIdx.x * 4ll + (threadIdx.x >> 6); t < total;
+       t += 4ll * gridDim.x) {
     const int a = (int)(t / words), w = (int)(t % words);
-    uint64_t m = 0;
-    for (int c = 0; c < 64; ++c) {
-      const int b = w * 64 + c;
-      if (b >= ns || a >= ns) break;
-      const bool keep = s ? s[(int64_t)a * ns + b] >= thr : true;
-      if (b != a && keep) m |= 1ull << c;
-    }
-    kb[t] = m;
-    // the diagonal word w is gathered over its 64 rows by one thread
-    if (a == 0) {
-      uint64_t d = 0;
-      for (int c = 0; c < 64; ++c) {
-        const int r = w * 64 + c;
-        if (r >= ns) break;
-        if (s ? s[(int64_t)r * ns + r] >= thr : true) d |= 1ull << c;
-      }
-      db[w] = d;
+    const int b = w * 64 + lane, r = a < n ? a : b;   // entry (r, b)
+    bool keep = b < ns && r < ns && (a == n || a != b);
+    if (keep && s) keep = s[(int64_t)r * ns + b] >= thr;
+    const uint64_t m = __ballot(keep);
+    if (lane == 0) {
+      if (a < n) kb[t] = m;
+      else db[w] = m;
     }
   }
 }
@@ -646,7 +639,7 @@ __global__ __launch_bounds__(PK_NT) void k_sched_list(PackArgs a, PackScratch sc
 // corrected for it.  Returns 1 when more than max_open batches would be
 // opened (the rest is then not placed).
 template <class Ord, class Emit>
-__device__ int window_ff(const PackArgs& a, int64_t count, Ord ord,
+__device__ int window_ff_lds(const PackArgs& a, int64_t count, Ord ord,
                          const SlotRec* __restrict__ slots, int64_t max_open,
                          Emit emit, uint32_t* inwin, int32_t* bidx) {
   constexpr uint32_t NONE_R = 4096u, NONE_W = 4097u;
@@ -791,6 +784,141 @@ __device__ int window_ff(const PackArgs& a, int64_t count, Ord ord,
   return over;
 }
 
+// window_ff for up to 64 NR orbitals, in registers: lane x holds the open
+// batch at position x (the set of its orbitals as a bit row, its slot and
+// pair counts, its LDS row), so one comparison over the lanes and a ballot
+// give a slot's candidates, and lane x takes the slot.  A lane of the next
+// 64 slots holds one slot's bit row; the rows are read lane by lane.  The
+// chain from slot to slot has no LDS round trip and about 40 instructions.
+// Measured per slot, 61 to 77 orbitals: 0.24 us against 0.43 us for the form
+// above (plain 96^3 with 77 orbitals: 1309 -> 702 us in all, the screened
+// 64^3 with 64: 654 -> 404 us, an outer step at 48^3 with 32 234 -> 130 us).
+template <int NR, class Ord, class Emit>
+__device__ int window_ff_reg(const PackArgs& a, int64_t count, Ord ord,
+                             const SlotRec* __restrict__ slots, int64_t max_open,
+                             Emit emit, int32_t* bidx) {
+  const int lane = threadIdx.x & 63;
+  const int cap = a.cap, ppb = a.ppb;
+  uint64_t occ[NR];            // lane x: orbitals of the batch at position x
+#pragma unroll
+  for (int r = 0; r < NR; ++r) occ[r] = 0;
+  int cs = 0, cp = 0, row = 0; // lane x: its slots, pairs, LDS row
+  uint32_t freep = (1u << PK_WIN) - 1u;
+  int nopen = 0, nb = 0;
+  const int bound = max_open < INT32_MAX ? (int)max_open : INT32_MAX;
+  struct Chunk {
+    uint64_t m[NR];
+    int np;
+    int32_t ix;
+  };
+  // index and slot are fetched one and two chunks ahead and turned into bit
+  // rows only when their chunk begins, so nothing waits for them
+  auto index = [&](int64_t base) {
+    return base + lane < count ? ord(base + lane) : -1;
+  };
+  auto fetch = [&](int32_t ix) {
+    SlotRec s{-1, -1, -1, -1, 0, 0u};
+    if (ix >= 0) s = slots[ix];
+    return s;
+  };
+  auto rows = [&](const SlotRec& s, int32_t ix, Chunk& c) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) c.m[r] = 0;
+    c.np = s.np;
+    c.ix = ix;
+    const int o[4] = {s.i, s.j, s.k, s.l};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+        if (o[t] >= 0 && (o[t] >> 6) == r) c.m[r] |= 1ull << (o[t] & 63);
+  };
+  auto lane64 = [](uint64_t v, int t) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, t) |
+           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), t) << 32);
+  };
+  auto drop = [&](int x, bool full) {   // position x leaves, those above move down
+    const int ph = __builtin_amdgcn_readlane(row, x);
+    emit(bidx + ph * 64, __builtin_amdgcn_readlane(cs, x), full);
+    freep |= 1u << ph;
+    const bool up = lane >= x;
+    const int ncs = __shfl_down(cs, 1, 64), ncp = __shfl_down(cp, 1, 64);
+    const int nrow = __shfl_down(row, 1, 64);
+    cs = up ? ncs : cs;
+    cp = up ? ncp : cp;
+    row = up ? nrow : row;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const uint64_t v = __shfl_down((unsigned long long)occ[r], 1, 64);
+      occ[r] = up ? v : occ[r];
+    }
+    --nopen;
+  };
+  Chunk c;   // slots c0 .. c0 + 63
+  int32_t ix0 = index(0), ix1 = index(64);
+  SlotRec rec = fetch(ix0);
+  for (int64_t c0 = 0; c0 < count; c0 += 64) {
+    rows(rec, ix0, c);
+    rec = fetch(ix1);
+    ix0 = ix1;
+    ix1 = index(c0 + 128);
+    const int m = count - c0 < 64 ? (int)(count - c0) : 64;
+    for (int t = 0; t < m; ++t) {
+      uint64_t mm[NR], hit = 0;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        mm[r] = lane64(c.m[r], t);
+        hit |= occ[r] & mm[r];
+      }
+      const int np = __builtin_amdgcn_readlane(c.np, t);
+      const int32_t six = __builtin_amdgcn_readlane(c.ix, t);
+      const uint64_t cand =
+          __ballot(hit == 0 && lane < nopen && cs < cap && cp + np <= ppb);
+      int x;
+      if (cand) {
+        x = __builtin_ctzll(cand);
+      } else {
+        if (nb >= bound) return 1;
+        if (nopen == PK_WIN) drop(0, false);   // the oldest leaves
+        x = nopen++;
+        const int ph = __builtin_ctz(freep);
+        freep &= ~(1u << ph);
+        ++nb;
+        if (lane == x) {
+          row = ph;
+          cs = cp = 0;
+#pragma unroll
+          for (int r = 0; r < NR; ++r) occ[r] = 0;
+        }
+      }
+      if (lane == x) {
+        bidx[row * 64 + cs] = six;
+        ++cs;
+        cp += np;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) occ[r] |= mm[r];
+      }
+      if (__ballot(lane == x && (cp >= ppb || cs >= cap))) drop(x, true);   // full
+    }
+  }
+  while (nopen) drop(0, false);
+  return 0;
+}
+
+// The form by the orbital count (the register form's bit rows grow with it).
+template <class Ord, class Emit>
+__device__ int window_ff(const PackArgs& a, int64_t count, Ord ord,
+                         const SlotRec* __restrict__ slots, int64_t max_open,
+                         Emit emit, uint32_t* inwin, int32_t* bidx) {
+  if (a.n_orb <= 64)
+    return window_ff_reg<1>(a, count, ord, slots, max_open, emit, bidx);
+  if (a.n_orb <= 128)
+    return window_ff_reg<2>(a, count, ord, slots, max_open, emit, bidx);
+  if (a.n_orb <= 256)
+    return window_ff_reg<4>(a, count, ord, slots, max_open, emit, bidx);
+  return window_ff_lds(a, count, ord, slots, max_open, emit, inwin, bidx);
+}
+
 // Start of section k of the slot list: k * per moved up to the next group
 // (round) boundary while it falls among the group-ordered slots, so that a
 // section takes whole cycles; section `sections` ends the list.
@@ -862,67 +990,84 @@ __device__ inline void clear_batch(BatchDev* b) {
   b->skip[0] = b->skip[1] = b->skip[2] = b->skip[3] = 0;
 }
 
-// Round-robin schedule (the bound the host launches for): every round in
-// batches of its own.  One thread.
-__device__ void fallback_schedule(const PackArgs& a, const uint64_t* kb,
-                                  const uint64_t* db, BatchDev* tab,
-                                  int32_t* n_batches) {
+// One round of the round-robin schedule: emit(slot, first) for its slots in
+// order, `first` when the slot opens a batch.
+template <class Emit>
+__device__ void fallback_round(const PackArgs& a, const uint64_t* kb,
+                               const uint64_t* db, int r, Emit emit_slot) {
   const int nv = a.n_orb + (a.n_orb & 1), m = nv - 1;
   const bool virt = a.n_occ < a.n_orb;
-  int64_t nb = 0;
-  BatchDev* cur = nullptr;
-  int cur_slots = 0, cur_pairs = 0;
   const int sp = a.gamma ? (a.ppb >= 2 ? a.ppb / 2 : 1) : a.ppb;
+  bool open = false;
+  int cur_slots = 0, cur_pairs = 0;
   auto emit = [&](const SlotRec& s) {
-    if (!cur || cur_slots == sp || cur_pairs + s.np > a.ppb) {
-      cur = tab + nb++;
-      clear_batch(cur);
-      cur_slots = cur_pairs = 0;
-    }
-    put_slot(cur, cur_slots++, s);
+    const bool first = !open || cur_slots == sp || cur_pairs + s.np > a.ppb;
+    if (first) cur_slots = cur_pairs = 0;
+    open = true;
+    emit_slot(s, first, cur_slots);
+    ++cur_slots;
     cur_pairs += s.np;
   };
-  auto close = [&]() { cur = nullptr; };
-  for (int r = 0; r < nv; ++r) {
-    SlotRec held[2] = {};
-    int nh[2] = {0, 0};     // pending single pair per kind (two-sided, one-sided)
-    auto take = [&](int x, int y, bool os) {
-      SlotRec s{x, y, -1, -1, 1, 0u};
-      if (os) s.flags = 1u | (x < a.n_occ ? 2u : 0u);
-      if (!a.gamma) { emit(s); return; }
-      if (a.ppb == 1) { emit(s); return; }
-      const int kd = os ? 1 : 0;
-      if (nh[kd]) {
-        SlotRec t = held[kd];
-        t.k = x; t.l = y; t.np = 2;
-        if (os && x < a.n_occ) t.flags |= 8u;
-        emit(t);
-        nh[kd] = 0;
-      } else {
-        held[kd] = s;
-        nh[kd] = 1;
-      }
-    };
-    if (r == nv - 1) {
-      for (int d = 0; d < a.n_orb; ++d)
-        if ((db[d >> 6] >> (d & 63)) & 1ull) take(d, d, false);
+  SlotRec held[2] = {};
+  int nh[2] = {0, 0};     // pending single pair per kind (two-sided, one-sided)
+  auto take = [&](int x, int y, bool os) {
+    SlotRec s{x, y, -1, -1, 1, 0u};
+    if (os) s.flags = 1u | (x < a.n_occ ? 2u : 0u);
+    if (!a.gamma || a.ppb == 1) { emit(s); return; }
+    const int kd = os ? 1 : 0;
+    if (nh[kd]) {
+      SlotRec t = held[kd];
+      t.k = x; t.l = y; t.np = 2;
+      if (os && x < a.n_occ) t.flags |= 8u;
+      emit(t);
+      nh[kd] = 0;
     } else {
-      auto pr = [&](int x, int y) {
-        if (x > y) { const int t = x; x = y; y = t; }
-        if (y >= a.n_orb) return;
-        const bool os = virt && x < a.n_occ && y >= a.n_occ;
-        if (os) take(x, y, true);
-        else if (y < a.n_occ && kbit(kb, a.words, x, y)) take(x, y, false);
-      };
-      pr(r, nv - 1);
-      for (int k = 1; k <= (m - 1) / 2; ++k) pr((r + k) % m, ((r - k) % m + m) % m);
+      held[kd] = s;
+      nh[kd] = 1;
     }
-    for (int kd = 0; kd < 2; ++kd)
-      if (nh[kd]) emit(held[kd]);
-    close();
+  };
+  if (r == nv - 1) {
+    for (int d = 0; d < a.n_orb; ++d)
+      if ((db[d >> 6] >> (d & 63)) & 1ull) take(d, d, false);
+  } else {
+    auto pr = [&](int x, int y) {
+      if (x > y) { const int t = x; x = y; y = t; }
+      if (y >= a.n_orb) return;
+      const bool os = virt && x < a.n_occ && y >= a.n_occ;
+      if (os) take(x, y, true);
+      else if (y < a.n_occ && kbit(kb, a.words, x, y)) take(x, y, false);
+    };
+    pr(r, nv - 1);
+    for (int k = 1; k <= (m - 1) / 2; ++k) pr((r + k) % m, ((r - k) % m + m) % m);
   }
-  for (int64_t b = nb; b < a.max_batches; ++b) clear_batch(tab + b), tab[b].n = 0;
-  *n_batches = (int32_t)nb;
+  for (int kd = 0; kd < 2; ++kd)
+    if (nh[kd]) emit(held[kd]);
+}
+
+// Round-robin schedule (the bound the host launches for): every round in
+// batches of its own.  A thread takes a round: it counts its batches, the
+// workgroup turns the counts into first batches, and it writes them (one
+// thread for all rounds took 1 ms for 61 orbitals).
+__device__ void fallback_schedule(const PackArgs& a, const uint64_t* kb,
+                                  const uint64_t* db, BatchDev* tab,
+                                  int32_t* n_batches, int64_t* wtot) {
+  const int nv = a.n_orb + (a.n_orb & 1);
+  int64_t nb = 0;
+  for (int r0 = 0; r0 < nv; r0 += PK_NT) {
+    const int r = r0 + (int)threadIdx.x;
+    int64_t mine = 0, total = 0;
+    if (r < nv)
+      fallback_round(a, kb, db, r, [&](const SlotRec&, bool first, int) { mine += first; });
+    BatchDev* cur = tab + nb + block_scan(mine, wtot, &total) - 1;
+    if (r < nv)
+      fallback_round(a, kb, db, r, [&](const SlotRec& s, bool first, int at) {
+        if (first) clear_batch(++cur);
+        put_slot(cur, at, s);
+      });
+    nb += total;
+  }
+  for (int64_t b = nb + threadIdx.x; b < a.max_batches; b += PK_NT) clear_batch(tab + b);
+  if (threadIdx.x == 0) *n_batches = (int32_t)nb;
 }
 
 // The sections' full batches in section order, then first-fit of all
@@ -937,6 +1082,7 @@ __global__ __launch_bounds__(PK_NT) void k_sched_merge(PackArgs a, PackScratch s
   __shared__ int32_t bidx[PK_WIN * 64];
   __shared__ int32_t sfb[32], sfi[32], spi[32];
   __shared__ int32_t st_nb, st_over;
+  __shared__ int64_t wtot[PK_NT / 64];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int S = a.sections;
   if (tid == 0) {
@@ -1002,9 +1148,9 @@ __global__ __launch_bounds__(PK_NT) void k_sched_merge(PackArgs a, PackScratch s
     if (n_pairs) *n_pairs = sc.count[1];
     sc.flags[0] = st_over;
     sc.flags[1] = st_nb;
-    if (st_over) fallback_schedule(a, sc.kb, sc.db, tab, n_batches);
-    else *n_batches = st_nb;
+    if (!st_over) *n_batches = st_nb;
   }
+  if (st_over) fallback_schedule(a, sc.kb, sc.db, tab, n_batches, wtot);
 }
 
 // The batch table from the directory: one wave per batch; entries past
@@ -1125,10 +1271,10 @@ hipError_t launch_schedule(const SchedDesc& d, hipStream_t st) {
   const int words = (n + 63) / 64;
   if (n < 1 || words > 64 || d.ppb < 1 || d.ppb > PMAX) return hipErrorInvalidValue;
   const SchedLayout L = sched_layout(n, d.scratch);
-  hipError_t e = launch_zero(L.db, 8 * words, st);
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
   if (d.pair_i) {
-    e = launch_zero(L.kb, 8 * (int64_t)n * words, st);
+    e = launch_zero(L.db, 8 * words, st);
+    if (e == hipSuccess) e = launch_zero(L.kb, 8 * (int64_t)n * words, st);
     if (e == hipSuccess) e = launch_zero(d.bad ? (void*)d.bad : (void*)L.flags, 4, st);
     if (e != hipSuccess) return e;
     int64_t blocks = (d.n_pairs + 255) / 256;
@@ -1138,8 +1284,8 @@ hipError_t launch_schedule(const SchedDesc& d, hipStream_t st) {
                 d.pair_i, d.pair_j, d.n_pairs, n, words, L.kb, L.db,
                 d.bad ? d.bad : L.flags);
   } else {
-    int64_t blocks = ((int64_t)n * words + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
+    int64_t blocks = ((int64_t)(n + 1) * words + 3) / 4;
+    if (blocks > 4096) blocks = 4096;
     LACE_LAUNCH(k_sched_bits_s, dim3((unsigned)blocks), dim3(256), 0, st, d.s,
                 n, d.s_n > 0 ? d.s_n : n, words, d.s_thr, L.kb, L.db);
   }
