@@ -18,8 +18,9 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liblace.so")
 OBJDIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["lace_api.hip", "fft_kernels.hip", "dense_kernels.hip", "polar_kernels.hip",
-           "scdm_kernels.hip", "screen_kernels.hip"]
+SOURCES = ["fft_f32.hip", "fft_f64.hip", "lace_api.hip", "fft_kernels.hip",
+           "dense_kernels.hip", "polar_kernels.hip", "scdm_kernels.hip",
+           "screen_kernels.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -499,13 +499,24 @@ __device__ inline int xcd_logical(int bid, int total) {
 template <int N> struct Pad { static constexpr int LS = N + 1; };
 
 // ------------------------------------------- xy-plane pass (whole plane)
-template <typename T, int N, int NT, int SIGN, class Pro, class Epi, int RO = 0>
+// GRP: the forward pass of a group of consecutive batches (pro reads them,
+// nslots is their slot capacity); slot q of batch b goes to buffer b nslots +
+// q of the group's pair buffers.
+template <typename T, int N, int NT, int SIGN, class Pro, class Epi, int RO = 0,
+          bool GRP = false>
 __global__ __launch_bounds__(NT) void k_plane(Pro pro, Epi epi,
                                               const C<T>* tw_g, int nslots) {
   constexpr int LS = Pad<N>::LS;
   __shared__ C<T> s[N * LS];
   __shared__ C<T> tw[N];
-  const int z = blockIdx.x, slot = blockIdx.y;
+  const int z = blockIdx.x;
+  int slot = blockIdx.y;
+  if constexpr (GRP) {
+    const int b = slot / nslots;
+    pro.bt += b;
+    epi.buf += (int64_t)b * nslots * epi.gs;
+    slot -= b * nslots;
+  }
   if (slot >= active_slots(pro, epi, nslots)) return;
   load_tw<T, N, NT>(tw, tw_g);
   const int base = z * N * N;
@@ -540,8 +551,9 @@ __global__ __launch_bounds__(NT) void k_plane(Pro pro, Epi epi,
 // SPLIT 2: the frequency split with a and b already formed by the previous
 // pass (the z pass) and stored as rows 0 .. H - 1 (a) and H .. N - 1 (b):
 // half h reads only its own contiguous half plane.
+// GRP: as k_plane's.
 template <typename T, int N, int NT, int MINW, int SIGN, class Pro, class Epi,
-          int SPLIT = 0, int RO = 0>
+          int SPLIT = 0, int RO = 0, bool GRP = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MINW)))
 void k_half(Pro pro, Epi epi, const C<T>* tw_g, int nslots) {
   constexpr int H = N / 2;
@@ -552,9 +564,16 @@ void k_half(Pro pro, Epi epi, const C<T>* tw_g, int nslots) {
   static_assert((H * N) % V == 0 && N % V == 0, "vector width");
   __shared__ C<T> s[H * LS];
   __shared__ C<T> tw[N];
+  int bid = blockIdx.x;
+  if constexpr (GRP) {
+    const int b = bid / (2 * N * nslots);
+    pro.bt += b;
+    epi.buf += (int64_t)b * nslots * epi.gs;
+    bid -= b * (2 * N * nslots);
+  }
   const int ns = active_slots(pro, epi, nslots);
-  if ((int)blockIdx.x >= 2 * N * ns) return;
-  const int lg = xcd_logical(blockIdx.x, 2 * N * ns);
+  if (bid >= 2 * N * ns) return;
+  const int lg = xcd_logical(bid, 2 * N * ns);
   const int half = lg & 1, zs = lg >> 1;
   const int z = zs % N, slot = zs / N;
   load_tw<T, N, NT>(tw, tw_g);
@@ -725,12 +744,15 @@ __device__ inline double block_sum(double v, double* red) {
 // b_k = (Y_k - Y_{k+N/2}) w^-k in row k + N/2, Y the result of the inverse
 // z transform, so that each half of the inverse xy pass reads only its own
 // half plane (its SPLIT 2 form).
+//
+// GRP: a group of consecutive batches of slot capacity `cap`, buffers and
+// energy cells by their slot in the group (SL = 1).
 template <typename T, int N, int TX, int SL, int NT, int MINW, int ORDER = 0,
-          bool DIT = false, int RO = 0>
+          bool DIT = false, int RO = 0, bool GRP = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(MINW)))
 void k_zconv(C<T>* __restrict__ tmp, int64_t gs, const T* __restrict__ vtab,
              const BatchDev* __restrict__ bt, double* epart, int ntiles,
-             const C<T>* tw_g) {
+             const C<T>* tw_g, int cap) {
   constexpr int LS = Pad<N>::LS;
   constexpr int NE1 = TX * N;          // points of one slot's tile
   constexpr int NE = SL * NE1;
@@ -740,10 +762,18 @@ void k_zconv(C<T>* __restrict__ tmp, int64_t gs, const T* __restrict__ vtab,
   __shared__ C<T> s[SL * TX * LS];
   __shared__ C<T> tw[N];
   __shared__ double red[NT / 64];
+  static_assert(!GRP || SL == 1, "one slot per workgroup in a group");
+  if constexpr (GRP) {
+    const int b = (int)blockIdx.x / (ntiles * cap);
+    bt += b;
+    tmp += (int64_t)b * cap * gs;
+    epart += (int64_t)b * cap * ntiles;
+  }
   const int nslots = bt->n;
   const int ngroups = (nslots + SL - 1) / SL;
-  if ((int)blockIdx.x >= ntiles * ngroups) return;
-  const int lg = xcd_logical(blockIdx.x, ntiles * ngroups);
+  const int bid = GRP ? (int)blockIdx.x % (ntiles * cap) : (int)blockIdx.x;
+  if (bid >= ntiles * ngroups) return;
+  const int lg = xcd_logical(bid, ntiles * ngroups);
   // ORDER 0: all slot groups of a tile together; 1: slot-group-major, the
   // last group first, so that the z pass ends on the slot that pass C
   // reads first (pass C after it measured 480 us against 486 us for order
@@ -919,15 +949,6 @@ void k_zconv(C<T>* __restrict__ tmp, int64_t gs, const T* __restrict__ vtab,
 }
 
 // ------------------------------------------------------------- helpers
-__global__ void k_zero(uint4* p, int64_t n16) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < n16;
-       k += stride)
-    p[k] = make_uint4(0u, 0u, 0u, 0u);
-}
-__global__ void k_zero_tail(unsigned char* p, int64_t n) {
-  for (int64_t k = threadIdx.x; k < n; k += blockDim.x) p[k] = 0;
-}
 
 template <typename T>
 __global__ void k_scatter(const double2* coeffs, int64_t n_pw,
@@ -955,26 +976,6 @@ __global__ void k_gather(const C<T>* w, int64_t gs, const int32_t* gidx,
     const C<T> v = w[j * gs + gidx[m]];
     out[k] = make_double2(scale * double(v.x), scale * double(v.y));
   }
-}
-
-// Thread t adds part[t], part[t + 256], ... in that order (16 loads in
-// flight per step, the additions still in order), then the workgroup sum.
-__global__ void k_reduce_sum(const double* part, int64_t count, double factor,
-                             double* out) {
-  __shared__ double red[256 / 64];
-  constexpr int U = 16;
-  double t = 0.0;
-  int64_t k = threadIdx.x;
-  for (; k + (U - 1) * 256 < count; k += U * 256) {
-    double v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = part[k + u * 256];
-#pragma unroll
-    for (int u = 0; u < U; ++u) t += v[u];
-  }
-  for (; k < count; k += 256) t += part[k];
-  const double tot = block_sum<256>(t, red);
-  if (threadIdx.x == 0) *out = factor * tot;
 }
 
 // ----------------------------------------------------- tile parameters
@@ -1069,8 +1070,65 @@ template <typename T, int N, int RO = 0> struct Engine {
     LACE_LAUNCH((k_zconv<T, N, TX, Cf::SL, Cf::NT_Z, MINW, 1, D, RO>),
                        dim3(ntiles * ((cnt + Cf::SL - 1) / Cf::SL)),
                        dim3(Cf::NT_Z), 0, st, tmp, NG, vtab, bt, epart,
-                       ntiles, tw);
+                       ntiles, tw, cnt);
     return hipGetLastError();
+  }
+  // A group of nb batches of slot capacity cap: one launch each for the
+  // passes A and B of all of them (their slots are independent and have
+  // buffers of their own), then pass C batch by batch, in the order that
+  // fixes the sums of W.  FP64 groups up to 48^3 only.
+  static constexpr bool group_ok = Cf::SL == 1 && (sizeof(T) == 4 || N <= 48);
+  template <bool D, int TX>
+  static hipError_t group_z(const BatchDev* bt, int nb, int cap, C<T>* tmp,
+                            double* epart, const T* vtab, const C<T>* tw,
+                            hipStream_t st) {
+    constexpr int ntiles = N * N / TX;
+    constexpr int MINW = TX > Cf::TXZ ? 2 : Cf::W_Z;
+    LACE_LAUNCH((k_zconv<T, N, TX, 1, Cf::NT_Z, MINW, 1, D, RO, true>),
+                dim3(ntiles * nb * cap), dim3(Cf::NT_Z), 0, st, tmp, NG, vtab, bt,
+                epart, ntiles, tw, cap);
+    return hipGetLastError();
+  }
+  template <bool D>
+  static hipError_t group_zt(int ztile, const BatchDev* bt, int nb, int cap, C<T>* tmp,
+                             double* epart, const T* vtab, const C<T>* tw,
+                             hipStream_t st) {
+    switch (ztile) {
+      case 1: return group_z<D, zt(1)>(bt, nb, cap, tmp, epart, vtab, tw, st);
+      case 2: return group_z<D, zt(2)>(bt, nb, cap, tmp, epart, vtab, tw, st);
+      default: return group_z<D, zt(0)>(bt, nb, cap, tmp, epart, vtab, tw, st);
+    }
+  }
+  template <class ProA, class EpiC>
+  static hipError_t run_group(const CellDev& c, ProA pa_, EpiC ec,
+                              const BatchDev* bt, int nb, int cap, C<T>* tmp,
+                              double* epart, hipStream_t st) {
+    if constexpr (group_ok) {
+      const C<T>* tw = static_cast<const C<T>*>(c.tw);
+      const T* vtab = static_cast<const T*>(c.vtab);
+      using EpiA = EpiSlotBuf<T>;
+      const EpiA ea{{tmp, NG, T(1)}};
+      const bool halves = c.use_plane == 2;
+      hipError_t err = hipErrorInvalidValue;
+      if (halves) {
+        LACE_LAUNCH((k_half<T, N, NT_HALF, W_HALF, -1, ProA, EpiA, XY_DIT ? 1 : 0, RO, true>),
+                    dim3(2 * N * nb * cap), dim3(NT_HALF), 0, st, pa_, ea, tw, cap);
+        err = group_zt<XY_DIT>(c.ztile, bt, nb, cap, tmp, epart, vtab, tw, st);
+      } else if constexpr (Cf::plane) {
+        LACE_LAUNCH((k_plane<T, N, Cf::NT_PLANE, -1, ProA, EpiA, RO, true>),
+                    dim3(N, nb * cap), dim3(Cf::NT_PLANE), 0, st, pa_, ea, tw, cap);
+        err = group_zt<false>(c.ztile, bt, nb, cap, tmp, epart, vtab, tw, st);
+      }
+      for (int b = 0; b < nb && err == hipSuccess; ++b) {
+        ec.bt = bt + b;
+        const ProSlotBuf<T> pb{{tmp + (int64_t)b * cap * NG, NG}};
+        err = halves ? half<+1, XY_DIT ? 2 : 0>(pb, ec, cap, tw, st)
+                     : plane<+1>(pb, ec, cap, tw, st);
+      }
+      return err;
+    } else {
+      return hipErrorInvalidValue;
+    }
   }
   template <bool D>
   static hipError_t zpass(C<T>* tmp, const T* vtab, const BatchDev* bt,
@@ -1217,6 +1275,19 @@ template <typename T, int N, int RO = 0> struct Engine {
                      bt, cap, tmp, epart, st, ev, sy);
   }
 
+  static hipError_t pair_group(const CellDev& c, const BatchDev* bt, int nb,
+                               int cap, const C<T>* psi, C<T>* w, C<T>* tmp,
+                               double* epart, hipStream_t st) {
+    return run_group(c, ProPair<T>{psi, NG, bt}, EpiAcc<T>{psi, w, NG, bt}, bt, nb,
+                     cap, tmp, epart, st);
+  }
+  static hipError_t quad_group(const CellDev& c, const BatchDev* bt, int nb,
+                               int cap, const T* psi, T* w, C<T>* tmp,
+                               double* epart, hipStream_t st) {
+    return run_group(c, ProQuadD<T>{psi, NG, bt}, EpiAccQuadD<T>{psi, w, NG, bt}, bt,
+                     nb, cap, tmp, epart, st);
+  }
+
   // energy partials per slot: enough for the smallest z tile
   static int64_t tiles() {
     const int a = zt(0), b = zt(1), c2 = zt(2);
@@ -1227,6 +1298,280 @@ template <typename T, int N, int RO = 0> struct Engine {
 
 // ------------------------------------------------------ runtime dispatch
 #define LACE_SIZES(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(80) X(96) X(120)
+
+// grid p <- C_{2p} + i C_{2p+1} on the sphere (zero elsewhere)
+template <typename T>
+__global__ void k_scatter_pairs(const double2* coeffs, int64_t n_pw,
+                                const int32_t* gidx, C<T>* z, int64_t gs,
+                                int n_orb) {
+  const int npair = (n_orb + 1) / 2;
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+  const int64_t total = n_pw * npair;
+  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < total;
+       k += stride) {
+    const int64_t p = k / n_pw, m = k % n_pw;
+    const double2 a = coeffs[(2 * p) * n_pw + m];
+    double2 b = make_double2(0.0, 0.0);
+    if (2 * p + 1 < n_orb) b = coeffs[(2 * p + 1) * n_pw + m];
+    z[p * gs + gidx[m]] = mk<T>(T(a.x - b.y), T(a.y + b.x));
+  }
+}
+
+// Unpack two real transforms: with Z = F[W_a + i W_b],
+// F[W_a](G) = (Z(G) + conj Z(-G)) / 2, F[W_b](G) = (Z(G) - conj Z(-G)) / 2i.
+template <typename T>
+__global__ void k_gather_pairs(const C<T>* z, int64_t gs, const int32_t* gidx,
+                               const int32_t* negidx, int64_t n_pw, int n_orb,
+                               double scale, double2* out) {
+  const int npair = (n_orb + 1) / 2;
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+  const int64_t total = n_pw * npair;
+  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < total;
+       k += stride) {
+    const int64_t p = k / n_pw, m = k % n_pw;
+    const C<T> a = z[p * gs + gidx[m]];
+    const C<T> b = z[p * gs + gidx[negidx[m]]];
+    const double ax = a.x, ay = a.y, bx = b.x, by = b.y;
+    out[(2 * p) * n_pw + m] =
+        make_double2(0.5 * scale * (ax + bx), 0.5 * scale * (ay - by));
+    if (2 * p + 1 < n_orb)
+      out[(2 * p + 1) * n_pw + m] =
+          make_double2(0.5 * scale * (ay + by), -0.5 * scale * (ax - bx));
+  }
+}
+
+static inline unsigned grid_for(int64_t total) {
+  int64_t blocks = (total + 255) / 256;
+  if (blocks > 16384) blocks = 16384;
+  if (blocks < 1) blocks = 1;
+  return (unsigned)blocks;
+}
+
+template <typename T>
+hipError_t fft3d_t(const CellDev& c, int sign, void* grids, int count,
+                          T scale, hipStream_t st) {
+  C<T>* g = static_cast<C<T>*>(grids);
+  const C<T>* tw = static_cast<const C<T>*>(c.tw);
+  switch (c.n) {
+#define X(NN)                                                            \
+  case NN:                                                               \
+    return sign < 0 ? Engine<T, NN>::template fft3d<-1>(g, count, scale, tw, \
+                                                         c.use_plane, st)   \
+                    : Engine<T, NN>::template fft3d<+1>(g, count, scale, tw, \
+                                                         c.use_plane, st);
+    LACE_SIZES(X)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T>
+hipError_t orb_to_grid_t(const CellDev& c, const void* coeffs,
+                                int n_orb, void* psi, hipStream_t st) {
+  const int64_t bytes = (int64_t)n_orb * c.ng * sizeof(C<T>);
+  hipError_t err = launch_zero(psi, bytes, st);
+  if (err != hipSuccess) return err;
+  const int64_t total = c.n_pw * n_orb;
+  int64_t blocks = (total + 255) / 256;
+  if (blocks > 16384) blocks = 16384;
+  LACE_LAUNCH((k_scatter<T>), dim3((unsigned)blocks), dim3(256), 0, st,
+                     static_cast<const double2*>(coeffs), c.n_pw, c.gidx,
+                     static_cast<C<T>*>(psi), c.ng, n_orb);
+  err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  return fft3d_t<T>(c, +1, psi, n_orb, T(1.0 / std::sqrt(c.omega)), st);
+}
+
+template <typename T>
+hipError_t grid_to_pw_t(const CellDev& c, void* w, int n_orb,
+                               void* w_pw, hipStream_t st) {
+  hipError_t err = fft3d_t<T>(c, -1, w, n_orb, T(1), st);
+  if (err != hipSuccess) return err;
+  const int64_t total = c.n_pw * n_orb;
+  int64_t blocks = (total + 255) / 256;
+  if (blocks > 16384) blocks = 16384;
+  LACE_LAUNCH((k_gather<T>), dim3((unsigned)blocks), dim3(256), 0, st,
+                     static_cast<const C<T>*>(w), c.ng, c.gidx, c.n_pw, n_orb,
+                     std::sqrt(c.omega) / double(c.ng),
+                     static_cast<double2*>(w_pw));
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t pair_batch_t(const CellDev& c, const BatchDev* bt, int cap,
+                               const void* psi, void* w, void* tmp,
+                               double* epart, hipStream_t st,
+                               hipEvent_t* ev, const BatchSync* sy) {
+  switch (c.n) {
+#define X(NN)                                                               \
+  case NN:                                                                  \
+    return c.radix ? Engine<T, NN, 1>::pair_batch(                          \
+                         c, bt, cap, static_cast<const C<T>*>(psi),         \
+                         static_cast<C<T>*>(w), static_cast<C<T>*>(tmp),    \
+                         epart, st, ev, sy)                                 \
+                   : Engine<T, NN, 0>::pair_batch(                          \
+                         c, bt, cap, static_cast<const C<T>*>(psi),         \
+                         static_cast<C<T>*>(w), static_cast<C<T>*>(tmp),    \
+                         epart, st, ev, sy);
+    LACE_SIZES(X)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T>
+hipError_t orb_to_grid_real_t(const CellDev& c, const void* coeffs,
+                                     int n_orb, void* psi, void* scratch,
+                                     hipStream_t st) {
+  // the packed coefficients go to the psi buffer (npair complex grids, the
+  // bytes of n_orb real ones), are transformed through scratch, and come
+  // back to psi as real grids
+  const int npair = (n_orb + 1) / 2;
+  C<T>* zin = static_cast<C<T>*>(psi);
+  hipError_t err = launch_zero(zin, (int64_t)npair * c.ng * sizeof(C<T>), st);
+  if (err != hipSuccess) return err;
+  LACE_LAUNCH((k_scatter_pairs<T>), dim3(grid_for(c.n_pw * npair)),
+                     dim3(256), 0, st, static_cast<const double2*>(coeffs),
+                     c.n_pw, c.gidx, zin, c.ng, n_orb);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  const T scale = T(1.0 / std::sqrt(c.omega));
+  C<T>* z = static_cast<C<T>*>(scratch);
+  T* out = static_cast<T*>(psi);
+  const C<T>* tw = static_cast<const C<T>*>(c.tw);
+  switch (c.n) {
+#define X(NN)                                                               \
+  case NN:                                                                  \
+    return Engine<T, NN>::to_real(zin, z, npair, scale, out, n_orb, tw,     \
+                                  c.use_plane, st);
+    LACE_SIZES(X)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T>
+hipError_t grid_to_pw_real_t(const CellDev& c, const void* w, int n_orb,
+                                    void* scratch, void* w_pw, hipStream_t st) {
+  const int npair = (n_orb + 1) / 2;
+  C<T>* z = static_cast<C<T>*>(scratch);
+  const C<T>* tw = static_cast<const C<T>*>(c.tw);
+  hipError_t err = hipErrorInvalidValue;
+  switch (c.n) {
+#define X(NN)                                                               \
+  case NN:                                                                  \
+    err = Engine<T, NN>::from_real(static_cast<const T*>(w), n_orb, z,      \
+                                   npair, tw, c.use_plane, st);             \
+    break;
+    LACE_SIZES(X)
+#undef X
+    default: break;
+  }
+  if (err != hipSuccess) return err;
+  LACE_LAUNCH((k_gather_pairs<T>), dim3(grid_for(c.n_pw * npair)),
+                     dim3(256), 0, st, static_cast<const C<T>*>(scratch), c.ng,
+                     c.gidx, c.negidx, c.n_pw, n_orb,
+                     std::sqrt(c.omega) / double(c.ng),
+                     static_cast<double2*>(w_pw));
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t quad_batch_t(const CellDev& c, const BatchDev* bt, int cap,
+                               const void* psi, void* w, void* tmp,
+                               double* epart, hipStream_t st, hipEvent_t* ev,
+                               const BatchSync* sy) {
+  switch (c.n) {
+#define X(NN)                                                                \
+  case NN:                                                                   \
+    return c.radix ? Engine<T, NN, 1>::quad_batch(                           \
+                         c, bt, cap, static_cast<const T*>(psi),             \
+                         static_cast<T*>(w), static_cast<C<T>*>(tmp), epart, \
+                         st, ev, sy)                                         \
+                   : Engine<T, NN, 0>::quad_batch(                           \
+                         c, bt, cap, static_cast<const T*>(psi),             \
+                         static_cast<T*>(w), static_cast<C<T>*>(tmp), epart, \
+                         st, ev, sy);
+    LACE_SIZES(X)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T>
+hipError_t group_t(const CellDev& c, bool real, const BatchDev* bt, int nb,
+                          int cap, const void* psi, void* w, void* tmp,
+                          double* epart, hipStream_t st) {
+  C<T>* t = static_cast<C<T>*>(tmp);
+  switch (c.n) {
+#define X(NN)                                                                  \
+  case NN:                                                                     \
+    if (real) {                                                                \
+      const T* p = static_cast<const T*>(psi);                                 \
+      T* q = static_cast<T*>(w);                                               \
+      return c.radix                                                           \
+                 ? Engine<T, NN, 1>::quad_group(c, bt, nb, cap, p, q, t, epart, st)  \
+                 : Engine<T, NN, 0>::quad_group(c, bt, nb, cap, p, q, t, epart, st); \
+    } else {                                                                   \
+      const C<T>* p = static_cast<const C<T>*>(psi);                           \
+      C<T>* q = static_cast<C<T>*>(w);                                         \
+      return c.radix                                                           \
+                 ? Engine<T, NN, 1>::pair_group(c, bt, nb, cap, p, q, t, epart, st)  \
+                 : Engine<T, NN, 0>::pair_group(c, bt, nb, cap, p, q, t, epart, st); \
+    }
+    LACE_SIZES(X)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// The kernels of one precision are compiled in a source of their own
+// (fft_f32.hip and fft_f64.hip define LACE_FFT_T and include this file), in
+// parallel; the launchers below refer to them.
+#define LACE_FFT_ENTRIES(X, T) \
+  X hipError_t fft3d_t<T>(const CellDev& c, int sign, void* grids, int count, T scale, hipStream_t st); \
+  X hipError_t orb_to_grid_t<T>(const CellDev& c, const void* coeffs, int n_orb, void* psi, hipStream_t st); \
+  X hipError_t grid_to_pw_t<T>(const CellDev& c, void* w, int n_orb, void* w_pw, hipStream_t st); \
+  X hipError_t pair_batch_t<T>(const CellDev& c, const BatchDev* bt, int cap, const void* psi, void* w, void* tmp, double* epart, hipStream_t st, hipEvent_t* ev, const BatchSync* sy); \
+  X hipError_t orb_to_grid_real_t<T>(const CellDev& c, const void* coeffs, int n_orb, void* psi, void* scratch, hipStream_t st); \
+  X hipError_t grid_to_pw_real_t<T>(const CellDev& c, const void* w, int n_orb, void* scratch, void* w_pw, hipStream_t st); \
+  X hipError_t quad_batch_t<T>(const CellDev& c, const BatchDev* bt, int cap, const void* psi, void* w, void* tmp, double* epart, hipStream_t st, hipEvent_t* ev, const BatchSync* sy); \
+  X hipError_t group_t<T>(const CellDev& c, bool real, const BatchDev* bt, int nb, int cap, const void* psi, void* w, void* tmp, double* epart, hipStream_t st);
+
+#ifdef LACE_FFT_T
+LACE_FFT_ENTRIES(template, LACE_FFT_T)
+#else
+LACE_FFT_ENTRIES(extern template, float)
+LACE_FFT_ENTRIES(extern template, double)
+
+__global__ void k_zero(uint4* p, int64_t n16) {
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < n16;
+       k += stride)
+    p[k] = make_uint4(0u, 0u, 0u, 0u);
+}
+__global__ void k_zero_tail(unsigned char* p, int64_t n) {
+  for (int64_t k = threadIdx.x; k < n; k += blockDim.x) p[k] = 0;
+}
+
+// Thread t adds part[t], part[t + 256], ... in that order (16 loads in
+// flight per step, the additions still in order), then the workgroup sum.
+__global__ void k_reduce_sum(const double* part, int64_t count, double factor,
+                             double* out) {
+  __shared__ double red[256 / 64];
+  constexpr int U = 16;
+  double t = 0.0;
+  int64_t k = threadIdx.x;
+  for (; k + (U - 1) * 256 < count; k += U * 256) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = part[k + u * 256];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t += v[u];
+  }
+  for (; k < count; k += 256) t += part[k];
+  const double tot = block_sum<256>(t, red);
+  if (threadIdx.x == 0) *out = factor * tot;
+}
 
 bool grid_supported(int n) {
   switch (n) {
@@ -1289,24 +1634,6 @@ int64_t energy_tiles(int n, bool fp64) {
   }
 }
 
-template <typename T>
-static hipError_t fft3d_t(const CellDev& c, int sign, void* grids, int count,
-                          T scale, hipStream_t st) {
-  C<T>* g = static_cast<C<T>*>(grids);
-  const C<T>* tw = static_cast<const C<T>*>(c.tw);
-  switch (c.n) {
-#define X(NN)                                                            \
-  case NN:                                                               \
-    return sign < 0 ? Engine<T, NN>::template fft3d<-1>(g, count, scale, tw, \
-                                                         c.use_plane, st)   \
-                    : Engine<T, NN>::template fft3d<+1>(g, count, scale, tw, \
-                                                         c.use_plane, st);
-    LACE_SIZES(X)
-#undef X
-    default: return hipErrorInvalidValue;
-  }
-}
-
 hipError_t launch_fft3d(const CellDev& c, bool fp64, int sign, void* grids,
                         int count, hipStream_t st) {
   return fp64 ? fft3d_t<double>(c, sign, grids, count, 1.0, st)
@@ -1329,23 +1656,6 @@ hipError_t launch_zero(void* p, int64_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t orb_to_grid_t(const CellDev& c, const void* coeffs,
-                                int n_orb, void* psi, hipStream_t st) {
-  const int64_t bytes = (int64_t)n_orb * c.ng * sizeof(C<T>);
-  hipError_t err = launch_zero(psi, bytes, st);
-  if (err != hipSuccess) return err;
-  const int64_t total = c.n_pw * n_orb;
-  int64_t blocks = (total + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  LACE_LAUNCH((k_scatter<T>), dim3((unsigned)blocks), dim3(256), 0, st,
-                     static_cast<const double2*>(coeffs), c.n_pw, c.gidx,
-                     static_cast<C<T>*>(psi), c.ng, n_orb);
-  err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  return fft3d_t<T>(c, +1, psi, n_orb, T(1.0 / std::sqrt(c.omega)), st);
-}
-
 hipError_t launch_orbitals_to_grid(const CellDev& c, bool fp64,
                                    const void* coeffs, int n_orb, void* psi,
                                    hipStream_t st) {
@@ -1353,47 +1663,10 @@ hipError_t launch_orbitals_to_grid(const CellDev& c, bool fp64,
               : orb_to_grid_t<float>(c, coeffs, n_orb, psi, st);
 }
 
-template <typename T>
-static hipError_t grid_to_pw_t(const CellDev& c, void* w, int n_orb,
-                               void* w_pw, hipStream_t st) {
-  hipError_t err = fft3d_t<T>(c, -1, w, n_orb, T(1), st);
-  if (err != hipSuccess) return err;
-  const int64_t total = c.n_pw * n_orb;
-  int64_t blocks = (total + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  LACE_LAUNCH((k_gather<T>), dim3((unsigned)blocks), dim3(256), 0, st,
-                     static_cast<const C<T>*>(w), c.ng, c.gidx, c.n_pw, n_orb,
-                     std::sqrt(c.omega) / double(c.ng),
-                     static_cast<double2*>(w_pw));
-  return hipGetLastError();
-}
-
 hipError_t launch_grid_to_pw(const CellDev& c, bool fp64, void* w, int n_orb,
                              void* w_pw, hipStream_t st) {
   return fp64 ? grid_to_pw_t<double>(c, w, n_orb, w_pw, st)
               : grid_to_pw_t<float>(c, w, n_orb, w_pw, st);
-}
-
-template <typename T>
-static hipError_t pair_batch_t(const CellDev& c, const BatchDev* bt, int cap,
-                               const void* psi, void* w, void* tmp,
-                               double* epart, hipStream_t st,
-                               hipEvent_t* ev, const BatchSync* sy) {
-  switch (c.n) {
-#define X(NN)                                                               \
-  case NN:                                                                  \
-    return c.radix ? Engine<T, NN, 1>::pair_batch(                          \
-                         c, bt, cap, static_cast<const C<T>*>(psi),         \
-                         static_cast<C<T>*>(w), static_cast<C<T>*>(tmp),    \
-                         epart, st, ev, sy)                                 \
-                   : Engine<T, NN, 0>::pair_batch(                          \
-                         c, bt, cap, static_cast<const C<T>*>(psi),         \
-                         static_cast<C<T>*>(w), static_cast<C<T>*>(tmp),    \
-                         epart, st, ev, sy);
-    LACE_SIZES(X)
-#undef X
-    default: return hipErrorInvalidValue;
-  }
 }
 
 hipError_t launch_pair_batch(const CellDev& c, bool fp64, const BatchDev* bt,
@@ -1413,83 +1686,6 @@ hipError_t launch_reduce_sum(const double* part, int64_t count, double factor,
 }
 
 // ------------------------------------------ real (Gamma-point) orbitals
-// grid p <- C_{2p} + i C_{2p+1} on the sphere (zero elsewhere)
-template <typename T>
-__global__ void k_scatter_pairs(const double2* coeffs, int64_t n_pw,
-                                const int32_t* gidx, C<T>* z, int64_t gs,
-                                int n_orb) {
-  const int npair = (n_orb + 1) / 2;
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  const int64_t total = n_pw * npair;
-  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < total;
-       k += stride) {
-    const int64_t p = k / n_pw, m = k % n_pw;
-    const double2 a = coeffs[(2 * p) * n_pw + m];
-    double2 b = make_double2(0.0, 0.0);
-    if (2 * p + 1 < n_orb) b = coeffs[(2 * p + 1) * n_pw + m];
-    z[p * gs + gidx[m]] = mk<T>(T(a.x - b.y), T(a.y + b.x));
-  }
-}
-
-// Unpack two real transforms: with Z = F[W_a + i W_b],
-// F[W_a](G) = (Z(G) + conj Z(-G)) / 2, F[W_b](G) = (Z(G) - conj Z(-G)) / 2i.
-template <typename T>
-__global__ void k_gather_pairs(const C<T>* z, int64_t gs, const int32_t* gidx,
-                               const int32_t* negidx, int64_t n_pw, int n_orb,
-                               double scale, double2* out) {
-  const int npair = (n_orb + 1) / 2;
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  const int64_t total = n_pw * npair;
-  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < total;
-       k += stride) {
-    const int64_t p = k / n_pw, m = k % n_pw;
-    const C<T> a = z[p * gs + gidx[m]];
-    const C<T> b = z[p * gs + gidx[negidx[m]]];
-    const double ax = a.x, ay = a.y, bx = b.x, by = b.y;
-    out[(2 * p) * n_pw + m] =
-        make_double2(0.5 * scale * (ax + bx), 0.5 * scale * (ay - by));
-    if (2 * p + 1 < n_orb)
-      out[(2 * p + 1) * n_pw + m] =
-          make_double2(0.5 * scale * (ay + by), -0.5 * scale * (ax - bx));
-  }
-}
-
-static unsigned grid_for(int64_t total) {
-  int64_t blocks = (total + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
-  if (blocks < 1) blocks = 1;
-  return (unsigned)blocks;
-}
-
-template <typename T>
-static hipError_t orb_to_grid_real_t(const CellDev& c, const void* coeffs,
-                                     int n_orb, void* psi, void* scratch,
-                                     hipStream_t st) {
-  // the packed coefficients go to the psi buffer (npair complex grids, the
-  // bytes of n_orb real ones), are transformed through scratch, and come
-  // back to psi as real grids
-  const int npair = (n_orb + 1) / 2;
-  C<T>* zin = static_cast<C<T>*>(psi);
-  hipError_t err = launch_zero(zin, (int64_t)npair * c.ng * sizeof(C<T>), st);
-  if (err != hipSuccess) return err;
-  LACE_LAUNCH((k_scatter_pairs<T>), dim3(grid_for(c.n_pw * npair)),
-                     dim3(256), 0, st, static_cast<const double2*>(coeffs),
-                     c.n_pw, c.gidx, zin, c.ng, n_orb);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-  const T scale = T(1.0 / std::sqrt(c.omega));
-  C<T>* z = static_cast<C<T>*>(scratch);
-  T* out = static_cast<T*>(psi);
-  const C<T>* tw = static_cast<const C<T>*>(c.tw);
-  switch (c.n) {
-#define X(NN)                                                               \
-  case NN:                                                                  \
-    return Engine<T, NN>::to_real(zin, z, npair, scale, out, n_orb, tw,     \
-                                  c.use_plane, st);
-    LACE_SIZES(X)
-#undef X
-    default: return hipErrorInvalidValue;
-  }
-}
 
 hipError_t launch_orbitals_to_grid_real(const CellDev& c, bool fp64,
                                         const void* coeffs, int n_orb,
@@ -1499,59 +1695,11 @@ hipError_t launch_orbitals_to_grid_real(const CellDev& c, bool fp64,
               : orb_to_grid_real_t<float>(c, coeffs, n_orb, psi, scratch, st);
 }
 
-template <typename T>
-static hipError_t grid_to_pw_real_t(const CellDev& c, const void* w, int n_orb,
-                                    void* scratch, void* w_pw, hipStream_t st) {
-  const int npair = (n_orb + 1) / 2;
-  C<T>* z = static_cast<C<T>*>(scratch);
-  const C<T>* tw = static_cast<const C<T>*>(c.tw);
-  hipError_t err = hipErrorInvalidValue;
-  switch (c.n) {
-#define X(NN)                                                               \
-  case NN:                                                                  \
-    err = Engine<T, NN>::from_real(static_cast<const T*>(w), n_orb, z,      \
-                                   npair, tw, c.use_plane, st);             \
-    break;
-    LACE_SIZES(X)
-#undef X
-    default: break;
-  }
-  if (err != hipSuccess) return err;
-  LACE_LAUNCH((k_gather_pairs<T>), dim3(grid_for(c.n_pw * npair)),
-                     dim3(256), 0, st, static_cast<const C<T>*>(scratch), c.ng,
-                     c.gidx, c.negidx, c.n_pw, n_orb,
-                     std::sqrt(c.omega) / double(c.ng),
-                     static_cast<double2*>(w_pw));
-  return hipGetLastError();
-}
-
 hipError_t launch_grid_to_pw_real(const CellDev& c, bool fp64,
                                   const void* w_real, int n_orb, void* scratch,
                                   void* w_pw, hipStream_t st) {
   return fp64 ? grid_to_pw_real_t<double>(c, w_real, n_orb, scratch, w_pw, st)
               : grid_to_pw_real_t<float>(c, w_real, n_orb, scratch, w_pw, st);
-}
-
-template <typename T>
-static hipError_t quad_batch_t(const CellDev& c, const BatchDev* bt, int cap,
-                               const void* psi, void* w, void* tmp,
-                               double* epart, hipStream_t st, hipEvent_t* ev,
-                               const BatchSync* sy) {
-  switch (c.n) {
-#define X(NN)                                                                \
-  case NN:                                                                   \
-    return c.radix ? Engine<T, NN, 1>::quad_batch(                           \
-                         c, bt, cap, static_cast<const T*>(psi),             \
-                         static_cast<T*>(w), static_cast<C<T>*>(tmp), epart, \
-                         st, ev, sy)                                         \
-                   : Engine<T, NN, 0>::quad_batch(                           \
-                         c, bt, cap, static_cast<const T*>(psi),             \
-                         static_cast<T*>(w), static_cast<C<T>*>(tmp), epart, \
-                         st, ev, sy);
-    LACE_SIZES(X)
-#undef X
-    default: return hipErrorInvalidValue;
-  }
 }
 
 hipError_t launch_quad_batch(const CellDev& c, bool fp64, const BatchDev* bt,
@@ -1561,6 +1709,16 @@ hipError_t launch_quad_batch(const CellDev& c, bool fp64, const BatchDev* bt,
   if (cap <= 0 || cap > SMAX) return hipErrorInvalidValue;
   return fp64 ? quad_batch_t<double>(c, bt, cap, psi, w, tmp, epart, st, ev, sy)
               : quad_batch_t<float>(c, bt, cap, psi, w, tmp, epart, st, ev, sy);
+}
+
+hipError_t launch_batch_group(const CellDev& c, bool fp64, bool real,
+                              const BatchDev* bt, int nb, int cap,
+                              const void* psi, void* w, void* tmp,
+                              double* epart, hipStream_t st) {
+  if (nb < 1 || cap < 1 || nb * cap > 2 * SMAX || c.use_plane == 0)
+    return hipErrorInvalidValue;
+  return fp64 ? group_t<double>(c, real, bt, nb, cap, psi, w, tmp, epart, st)
+              : group_t<float>(c, real, bt, nb, cap, psi, w, tmp, epart, st);
 }
 
 // per block: sum |C_m - conj C_{-m}|^2 and sum |C_m|^2 over its share
@@ -1605,5 +1763,7 @@ hipError_t launch_real_check(const CellDev& c, const void* coeffs, int n_orb,
                      c.negidx, part);
   return hipGetLastError();
 }
+
+#endif  // LACE_FFT_T
 
 }  // namespace lace

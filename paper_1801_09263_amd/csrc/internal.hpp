@@ -112,6 +112,14 @@ hipError_t launch_quad_batch(const CellDev& c, bool fp64, const BatchDev* bt,
                              int cap, const void* psi_real, void* w_real,
                              void* tmp, double* epart, hipStream_t st,
                              hipEvent_t* ev, const BatchSync* sy = nullptr);
+// nb consecutive batches of slot capacity cap at once (nb cap <= 2 SMAX;
+// half-plane or whole-plane schedule; FP64 up to 48^3): the passes A and B of
+// all of them in one launch each, then pass C batch by batch.  tmp: nb cap pair buffers,
+// epart: nb cap energy_tiles energy cells.
+hipError_t launch_batch_group(const CellDev& c, bool fp64, bool real,
+                              const BatchDev* bt, int nb, int cap,
+                              const void* psi, void* w, void* tmp,
+                              double* epart, hipStream_t st);
 // Sum over orbitals of sum_m |C_m - conj(C_{-m})|^2 and sum_m |C_m|^2 into
 // part[2 * nblocks] (host reduces); returns the number of blocks used.
 hipError_t launch_real_check(const CellDev& c, const void* coeffs, int n_orb,
@@ -248,6 +256,21 @@ inline hipError_t launch_polar(const void*, bool, int n, void* ya, void* yb,
   for (void* p : {ya, yb, b, U}) std::memset(p, 0x3c, 16 * (size_t)n * n);
   std::memset(state, 0, (size_t)polar_state_bytes());
   if (resid) *resid = 0.0;
+  return hipSuccess;
+}
+inline hipError_t launch_batch_group(const CellDev& c, bool fp64, bool real,
+                                     const BatchDev* bt, int nb, int cap,
+                                     const void* psi, void* w, void* tmp,
+                                     double* epart, hipStream_t st) {
+  const int64_t g = c.ng * (fp64 ? 16 : 8);
+  for (int b = 0; b < nb; ++b) {
+    char* t = static_cast<char*>(tmp) + (int64_t)b * cap * g;
+    double* e = epart + (int64_t)b * cap * energy_tiles(c.n, fp64);
+    const hipError_t r =
+        real ? launch_quad_batch(c, fp64, bt + b, cap, psi, w, t, e, st, nullptr)
+             : launch_pair_batch(c, fp64, bt + b, cap, psi, w, t, e, st, nullptr);
+    if (r != hipSuccess) return r;
+  }
   return hipSuccess;
 }
 inline hipError_t launch_scdm(bool, bool, const void* psi, int n_orb, int64_t ng,

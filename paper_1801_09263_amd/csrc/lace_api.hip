@@ -589,6 +589,39 @@ static int slot_cap(const lace_plan* p, int ppb) {
   return p->gamma ? (ppb + 1) / 2 : ppb;
 }
 
+// The most slots a batch of n_orb orbitals can hold: no orbital is in two
+// slots, a slot of real orbitals holds two or more (but one slot with a
+// single diagonal pair), one of complex orbitals one or more.
+static int batch_slots(const lace_plan* p, int n_orb, int ppb) {
+  const int most = p->gamma ? (n_orb + 1) / 2 : n_orb;
+  return std::min(slot_cap(p, ppb), ppb == 1 ? 1 : most);
+}
+
+// Batches per group, 0 for batch by batch.  A group runs the passes A and B
+// of all its batches in one launch each, on one stream, in the pair buffers
+// of both lanes.  It replaces the two-stream pipeline (two) while the pair
+// buffers of one batch stay below a size, from which on the launches of
+// single batches fill the chip and the overlap of two streams gains more.
+// Measured, whole exchange, two streams -> groups (bytes of one batch's
+// buffers), real FP32: 12^3 with 2 orbitals 266 -> 88 us, 24^3 / 16 593 ->
+// 190 us, 48^3 / 32 (14 MB) 1134 -> 768 us, 64^3 / 64 (34 MB) 4.55 -> 4.16
+// ms, 80^3 / 96 (66 MB) 16.2 -> 15.3 ms, 96^3 / 128 (113 MB) 25.8 -> 24.4
+// ms; with larger batches 80^3 / 96 (131 MB) 14.4 -> 15.3 ms, 120^3 / 256
+// (221 and 442 MB) 317 -> 328 and 314 -> 322 ms.  FP64: 48^3 / 16 complex (28
+// MB) 798 -> 704 us, 32 real (28 MB) 1335 -> 1155 us, 24 complex (42 MB) 1427
+// -> 1511 us, 64^3 (67 MB) 5.25 -> 5.28 ms.  On one stream (a batched call's
+// jobs) groups replace single batches of any size: 8 cells 84.2 -> 79.1 ms.
+static int group_batches(const lace_plan* p, const CellDev& c, int n_orb, int ppb,
+                         bool two) {
+  if (c.use_plane == 0 || (c.use_plane == 1 && !plane_fits(c.n, p->fp64))) return 0;
+  if (p->fp64 && c.n > 48) return 0;   // no group kernels there
+  const int slots = batch_slots(p, n_orb, ppb);
+  const double bytes = (double)slots * (double)c.ng * (double)grid_bytes(p);
+  if (two && bytes > (p->fp64 ? 32e6 : 120e6)) return 0;
+  const int g = 2 * SMAX / slots;
+  return g >= 2 ? g : 0;
+}
+
 // Batch b of the workspace's batch table through the pair pipeline.
 // `lane` picks the pair buffer and the energy partials (0 or 1).
 static hipError_t enqueue_batch(const lace_plan* p, const CellDev& c,
@@ -680,9 +713,21 @@ static hipError_t enqueue_schedule(const lace_plan* p, const CellDev& c,
 // and B overlapping the previous batch's pass C, the C passes in batch
 // order; the caller's stream waits for both lanes at the end.  Else all on
 // the caller's stream.
-static hipError_t enqueue_batches(lace_plan* p, const CellDev& c, int64_t nb,
-                                  int ppb, const Layout& L, void* ws,
+// Where group_batches says so, in groups of batches on the caller's stream.
+static hipError_t enqueue_batches(lace_plan* p, const CellDev& c, int n_orb,
+                                  int64_t nb, int ppb, const Layout& L, void* ws,
                                   hipStream_t st, bool two) {
+  if (const int g = group_batches(p, c, n_orb, ppb, two)) {
+    // both lanes' pair buffers and energy cells, on the caller's stream
+    const int cap = batch_slots(p, n_orb, ppb);
+    hipError_t e = hipSuccess;
+    for (int64_t b = 0; e == hipSuccess && b < nb; b += g)
+      e = launch_batch_group(
+          c, p->fp64, p->gamma, reinterpret_cast<const BatchDev*>(at(ws, L.tab)) + b,
+          (int)std::min<int64_t>(g, nb - b), cap, at(ws, L.psi), at(ws, L.w),
+          at(ws, L.tmp), reinterpret_cast<double*>(at(ws, L.epart)), st);
+    return e;
+  }
   two = two && nb > 1;
   hipStream_t lane[2] = {st, st};
   hipEvent_t cdone[2] = {nullptr, nullptr};
@@ -769,7 +814,7 @@ static hipError_t enqueue_exchange(lace_plan* p, const CellDev& c, int n_orb,
       e = enqueue_batch(p, c, b, ppb, L, ws, (int)(b % 2), st, ev);
     }
   } else if (e == hipSuccess) {
-    e = enqueue_batches(p, c, nb, ppb, L, ws, st, two);
+    e = enqueue_batches(p, c, n_orb, nb, ppb, L, ws, st, two);
   }
   if (e == hipSuccess && e_x)
     e = launch_reduce_sum(epart, (int64_t)PMAX * 2 * ntiles,
@@ -1558,7 +1603,7 @@ int lace_autotune(lace_plan* p, int cell, const void* psi_g, int n_orb,
     double best = 1e30;
     for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
       e = hipEventRecord(t0, st);
-      if (e == hipSuccess) e = enqueue_batches(p, c, (int64_t)nb, cd.ppb, L, ws, st, true);
+      if (e == hipSuccess) e = enqueue_batches(p, c, n_orb, (int64_t)nb, cd.ppb, L, ws, st, true);
       if (e == hipSuccess) e = hipEventRecord(t1, st);
       if (e == hipSuccess) e = hipEventSynchronize(t1);
       float ms = 0.f;
