@@ -623,16 +623,21 @@ static int group_batches(const lace_plan* p, const CellDev& c, int n_orb, int pp
 }
 
 // Batch b of the workspace's batch table through the pair pipeline.
-// `lane` picks the pair buffer and the energy partials (0 or 1).
-static hipError_t enqueue_batch(const lace_plan* p, const CellDev& c,
+// `lane` picks the pair buffer (0 or 1).  The energy cells of batch b are
+// those of its place in a group of 2 SMAX / slots batches, however the
+// batches are launched, so that E_x is the same sum in every mode.  (Two
+// batches that share cells are at least two apart, and more when they are
+// on different lanes: the order of the C passes keeps them apart.)
+static hipError_t enqueue_batch(const lace_plan* p, const CellDev& c, int n_orb,
                                 int64_t b, int ppb, const Layout& L, void* ws,
                                 int lane, hipStream_t st, hipEvent_t* ev,
                                 const BatchSync* sy = nullptr) {
   void* tmp = at(ws, L.tmp + (size_t)lane * SMAX * c.ng * grid_bytes(p));
+  const int cap = batch_slots(p, n_orb, ppb);
+  const int64_t tiles = (int64_t)c.n * c.n / ztile_points(c.n, p->fp64, c.ztile);
   double* epart = reinterpret_cast<double*>(at(ws, L.epart)) +
-                  (size_t)lane * PMAX * energy_tiles(c.n, p->fp64);
+                  (b % (2 * SMAX / cap)) * cap * tiles;
   const BatchDev* bt = reinterpret_cast<const BatchDev*>(at(ws, L.tab)) + b;
-  const int cap = slot_cap(p, ppb);
   if (p->gamma)
     return launch_quad_batch(c, p->fp64, bt, cap, at(ws, L.psi), at(ws, L.w),
                              tmp, epart, st, ev, sy);
@@ -746,10 +751,10 @@ static hipError_t enqueue_batches(lace_plan* p, const CellDev& c, int n_orb,
   for (int64_t b = 0; e == hipSuccess && b < nb; ++b) {
     if (two) {
       BatchSync sy{b > 0 ? cdone[(b - 1) % 2] : nullptr, cdone[b % 2]};
-      e = enqueue_batch(p, c, b, ppb, L, ws, (int)(b % 2), lane[b % 2], nullptr,
-                        &sy);
+      e = enqueue_batch(p, c, n_orb, b, ppb, L, ws, (int)(b % 2), lane[b % 2],
+                        nullptr, &sy);
     } else {
-      e = enqueue_batch(p, c, b, ppb, L, ws, (int)(b % 2), st, nullptr);
+      e = enqueue_batch(p, c, n_orb, b, ppb, L, ws, (int)(b % 2), st, nullptr);
     }
   }
   if (e == hipSuccess && two) {
@@ -811,7 +816,7 @@ static hipError_t enqueue_exchange(lace_plan* p, const CellDev& c, int n_orb,
       r.pairs = host_tab[(size_t)b].npairs;
       batch_bytes(p, c, host_tab[(size_t)b], r.bytes);
       pr.recs.push_back(r);
-      e = enqueue_batch(p, c, b, ppb, L, ws, (int)(b % 2), st, ev);
+      e = enqueue_batch(p, c, n_orb, b, ppb, L, ws, (int)(b % 2), st, ev);
     }
   } else if (e == hipSuccess) {
     e = enqueue_batches(p, c, n_orb, nb, ppb, L, ws, st, two);

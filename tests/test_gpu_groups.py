@@ -46,6 +46,5 @@ def test_group_equals_batches(prec, n, L, n_orb, virt, tuning):
     for w, e, kept in out[1:]:
         assert torch.equal(w, out[0][0])
         assert kept == out[0][2]
-        # the energy cells are summed in another order
-        assert abs(e - out[0][1]) <= 1e-13 * abs(e)
+        assert e == out[0][1]
     assert torch.isfinite(torch.view_as_real(out[0][0])).all()
