@@ -860,79 +860,121 @@ hipError_t launch_neg_sym(const void* M, int n, int mode, void* A,
 // pivot is kept in info; later blocks see it and do nothing.
 constexpr int CB = 64;
 
+// The diagonal block in registers: thread (ti, tj) of 16 x 16 holds the
+// elements (ti + 16 a, tj + 16 b).  Columns stay unscaled until the end
+// (A_ij -= A_ik conj(A_jk) / d_k), so a step is one exchange of column k
+// through LDS and one barrier (two buffers).  64 columns 93 -> 38 us (three
+// barriers a step and the block in LDS before).
 __global__ __launch_bounds__(256) void k_chol_diag(double2* A, int n, int k0,
                                                    int kb, int32_t* info) {
-  __shared__ double2 a[CB][CB + 1];
-  __shared__ int fail;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < kb * kb; e += 256) {
-    const int i = e / kb, j = e % kb;
-    a[i][j] = A[(int64_t)(k0 + i) * n + k0 + j];
+  __shared__ double2 col[2][CB];
+  __shared__ double diag[CB];
+  const int tid = threadIdx.x, ti = tid / 16, tj = tid % 16;
+  if (*info != 0) return;
+  double2 v[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int i = ti + 16 * a, j = tj + 16 * b;
+      v[a][b] = make_double2(0.0, 0.0);
+      if (i < kb && j < kb) v[a][b] = A[(int64_t)(k0 + i) * n + k0 + j];
+    }
+#pragma unroll
+  for (int bk = 0; bk < 4; ++bk) {
+    for (int kk = 0; kk < 16; ++kk) {
+      const int k = 16 * bk + kk;
+      if (k >= kb) break;
+      double2* c = col[k & 1];
+      if (tj == kk) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) c[ti + 16 * a] = v[a][bk];
+      }
+      __syncthreads();
+      const double d = c[k].x;
+      if (!(d > 0.0)) {   // every thread reads the same pivot
+        if (tid == 0) *info = k0 + k + 1;
+        return;
+      }
+      if (tid == 0) diag[k] = d;
+      const double inv = 1.0 / d;
+      double2 ci[4], cj[4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        ci[a] = c[ti + 16 * a];
+        const double2 t = c[tj + 16 * a];
+        cj[a] = make_double2(t.x * inv, t.y * inv);
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          if (ti + 16 * a <= k || tj + 16 * b <= k) continue;
+          v[a][b].x -= ci[a].x * cj[b].x + ci[a].y * cj[b].y;
+          v[a][b].y -= ci[a].y * cj[b].x - ci[a].x * cj[b].y;
+        }
+    }
   }
-  if (tid == 0) fail = (*info != 0) ? -1 : 0;
   __syncthreads();
-  if (fail) return;
-  for (int k = 0; k < kb; ++k) {
-    if (tid == 0) {
-      const double d = a[k][k].x;
-      if (!(d > 0.0)) fail = k0 + k + 1;
-      else a[k][k] = make_double2(sqrt(d), 0.0);
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int i = ti + 16 * a, j = tj + 16 * b;
+      if (i >= kb || j > i) continue;
+      const double r = sqrt(diag[j]);
+      A[(int64_t)(k0 + i) * n + k0 + j] =
+          i == j ? make_double2(r, 0.0) : make_double2(v[a][b].x / r, v[a][b].y / r);
     }
-    __syncthreads();
-    if (fail) break;
-    const double inv = 1.0 / a[k][k].x;
-    for (int i = k + 1 + tid; i < kb; i += 256)
-      a[i][k] = make_double2(a[i][k].x * inv, a[i][k].y * inv);
-    __syncthreads();
-    const int m = kb - k - 1;
-    for (int e = tid; e < m * m; e += 256) {
-      const int i = k + 1 + e / m, j = k + 1 + e % m;
-      if (j > i) continue;
-      const double2 li = a[i][k], lj = a[j][k];
-      a[i][j].x -= li.x * lj.x + li.y * lj.y;
-      a[i][j].y -= li.y * lj.x - li.x * lj.y;
-    }
-    __syncthreads();
-  }
-  if (fail) {
-    if (tid == 0) *info = fail;
-    return;
-  }
-  for (int e = tid; e < kb * kb; e += 256) {
-    const int i = e / kb, j = e % kb;
-    if (j <= i) A[(int64_t)(k0 + i) * n + k0 + j] = a[i][j];
-  }
 }
 
 // Rows i >= k0 + kb of the panel: x L_kk^H = a, i.e. forward substitution
-// x_j = (a_j - sum_{m<j} x_m conj(L_jm)) / L_jj; one thread per row, 64 rows
-// per workgroup, the rows' solutions in LDS.
-constexpr int CP_ROWS = 64;
-__global__ __launch_bounds__(CP_ROWS) void k_chol_panel(double2* A, int n, int k0,
-                                                        int kb, const int32_t* info) {
+// x_j = (a_j - sum_{m<j} x_m conj(L_jm)) / L_jj; 64 rows per workgroup, the
+// rows' solutions in LDS, eight lanes a row, each with every eighth m (one
+// thread a row took 80 us for 64 columns, this 45).
+constexpr int CP_ROWS = 64, CP_G = 8;
+__global__ __launch_bounds__(CP_ROWS * CP_G) void k_chol_panel(
+    double2* A, int n, int k0, int kb, const int32_t* info) {
   __shared__ double2 l[CB][CB + 1];
   __shared__ double2 xs[CP_ROWS][CB + 1];
-  for (int e = threadIdx.x; e < kb * kb; e += CP_ROWS) {
-    const int i = e / kb, j = e % kb;
-    l[i][j] = A[(int64_t)(k0 + i) * n + k0 + j];
+  __shared__ double inv[CB];
+  const int tid = threadIdx.x;
+  if (*info != 0) return;
+  const int t = tid / CP_G, g = tid % CP_G;
+  const int r0 = k0 + kb + blockIdx.x * CP_ROWS;
+  for (int e = tid; e < CB * CB; e += CP_ROWS * CP_G) {
+    const int i = e / CB, j = e % CB;
+    if (i < kb && j <= i) l[i][j] = A[(int64_t)(k0 + i) * n + k0 + j];
+    if (j < kb && r0 + i < n) xs[i][j] = A[(int64_t)(r0 + i) * n + k0 + j];
   }
   __syncthreads();
-  if (*info != 0) return;
-  const int t = threadIdx.x;
-  const int i = k0 + kb + blockIdx.x * CP_ROWS + t;
-  if (i >= n) return;
-  double2* row = A + (int64_t)i * n + k0;
-  for (int j = 0; j < kb; ++j) {
-    double2 s = row[j];
-    for (int m = 0; m < j; ++m) {
-      const double2 L = l[j][m], x = xs[t][m];   // s -= x_m conj(L_jm)
-      s.x -= x.x * L.x + x.y * L.y;
-      s.y -= x.y * L.x - x.x * L.y;
+  for (int j = tid; j < kb; j += CP_ROWS * CP_G) inv[j] = 1.0 / l[j][j].x;
+  __syncthreads();
+  if (r0 + t < n) {
+    // the eight lanes of a row run in step within one wave
+    for (int j = 0; j < kb; ++j) {
+      double2 s = make_double2(0.0, 0.0);
+      for (int m = g; m < j; m += CP_G) {
+        const double2 L = l[j][m], x = xs[t][m];   // s += x_m conj(L_jm)
+        s.x += x.x * L.x + x.y * L.y;
+        s.y += x.y * L.x - x.x * L.y;
+      }
+#pragma unroll
+      for (int o = 1; o < CP_G; o <<= 1) {
+        s.x += __shfl_xor(s.x, o, 64);
+        s.y += __shfl_xor(s.y, o, 64);
+      }
+      if (g == j % CP_G) {   // the lane that reads x_j in later steps
+        const double2 a = xs[t][j];
+        xs[t][j] = make_double2((a.x - s.x) * inv[j], (a.y - s.y) * inv[j]);
+      }
     }
-    const double inv = 1.0 / l[j][j].x;
-    xs[t][j] = make_double2(s.x * inv, s.y * inv);
   }
-  for (int j = 0; j < kb; ++j) row[j] = xs[t][j];
+  __syncthreads();
+  for (int e = tid; e < CP_ROWS * kb; e += CP_ROWS * CP_G) {
+    const int i = e / kb, j = e % kb;
+    if (r0 + i < n) A[(int64_t)(r0 + i) * n + k0 + j] = xs[i][j];
+  }
 }
 
 __global__ void k_set_zero(int32_t* v) { *v = 0; }
@@ -976,7 +1018,7 @@ hipError_t launch_cholesky(void* Av, int n, int32_t* info, void* tmp,
     const int off = k0 + kb, m = n - off;
     if (e != hipSuccess || m <= 0) continue;
     LACE_LAUNCH(k_chol_panel, dim3((m + CP_ROWS - 1) / CP_ROWS),
-                       dim3(CP_ROWS), 0, st, A, n, k0, kb, info);
+                       dim3(CP_ROWS * CP_G), 0, st, A, n, k0, kb, info);
     e = hipGetLastError();
     // T[a][b] = sum_t conj(L[off + a][k0 + t]) L[off + b][k0 + t]
     if (e == hipSuccess)
@@ -1013,10 +1055,33 @@ __global__ __launch_bounds__(64) void k_trinv_adj(const double2* L, int n,
   __syncthreads();
   if (l == 0) x[c] = make_double2(1.0 / L[(int64_t)c * n + c].x, 0.0);
   __syncthreads();
+  // up to 256 entries of a row wait in registers, the next row's are on
+  // their way while this one is used (the rows do not depend on x)
+  constexpr int PF = 4;
+  double2 nx[PF];
+  auto fetch = [&](int i) {
+    const double2* row = L + (int64_t)min(i, n - 1) * n;
+#pragma unroll
+    for (int q = 0; q < PF; ++q) nx[q] = row[min(c + l + 64 * q, n - 1)];
+  };
+  fetch(c + 1);
   for (int i = c + 1; i < n; ++i) {
+    double2 cur[PF];
+#pragma unroll
+    for (int q = 0; q < PF; ++q) cur[q] = nx[q];
+    fetch(i + 1);
     double sr = 0.0, si = 0.0;
     const double2* row = L + (int64_t)i * n;
-    for (int m = c + l; m < i; m += 64) {
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+      const int m = c + l + 64 * q;
+      if (m < i) {
+        const double2 a = cur[q], b = x[m];
+        sr += a.x * b.x - a.y * b.y;
+        si += a.x * b.y + a.y * b.x;
+      }
+    }
+    for (int m = c + l + 64 * PF; m < i; m += 64) {
       const double2 a = row[m], b = x[m];
       sr += a.x * b.x - a.y * b.y;
       si += a.x * b.y + a.y * b.x;
