@@ -982,7 +982,12 @@ __global__ void k_gather(const C<T>* w, int64_t gs, const int32_t* gidx,
 template <typename T, int N> struct Cfg {
   // plane pass: whole N x N plane in LDS
   static constexpr bool plane = (int64_t)N * N * sizeof(C<T>) <= 150 * 1024;
-  static constexpr int NT_PLANE = sizeof(T) == 4 ? 1024 : 512;
+  // Threads: a stage of a length-48 plane has 192 or 576 butterflies, of a
+  // length-32 one 128 or 256; more threads than that only add waves to every
+  // barrier.  Measured, whole exchange, 1024 -> 256 threads: 48^3 complex
+  // FP32 with 32 orbitals 1431 -> 1299 us, 32^3 real FP32 with 20 265 -> 254;
+  // 24^3 and below and 64^3 with 512 were up to 15% slower.
+  static constexpr int NT_PLANE = sizeof(T) == 4 ? (N == 32 || N == 48 ? 256 : 1024) : 512;
   // y/z pencils: TX columns (>= 128 bytes of x per row when N allows)
   static constexpr int TX0 = sizeof(T) == 4 ? 16 : 8;
   static constexpr int TX = (N % TX0 == 0) ? TX0 : ((N % 8 == 0) ? 8 : 4);
@@ -1027,7 +1032,11 @@ template <typename T, int N, int RO = 0> struct Engine {
       return hipErrorInvalidValue;
     }
   }
-  static constexpr int NT_HALF = 512;
+  // 256 threads where a half plane's stages have at most 256 butterflies and
+  // it pays: 32^3 real FP32 274 -> 262 us, 64^3 real FP64 with 51 orbitals
+  // 5.12 -> 4.82 ms a whole exchange (64^3 FP32: 4.14 -> 4.22 ms)
+  static constexpr int NT_HALF = (sizeof(T) == 4 && N == 32) || (sizeof(T) == 8 && N == 64)
+                                     ? 256 : 512;
   // waves per SIMD to budget registers for: two workgroups of 8 waves when
   // two half planes fit the 160 KiB of LDS of a CU
   static constexpr int W_HALF =
