@@ -434,84 +434,108 @@ __global__ void k_lazy_init(LazyCtl* c, double* pv) {
 }
 
 // The directions [s, k) that 16 MP points have missed, applied to their d by
-// one wave on the matrix cores: q_m^T psi for 16 MD directions m at a time.
+// one wave on the matrix cores: q_m^T psi for 16 directions m at a time.
 // Lane l supplies QT[n + l / 16][m0 + l % 16] and the entry of orbital n +
 // l / 16 at point l % 16 of each 16; col + n ld: those entries, the last at
 // position `last`.  on, dv, s:
 // lane l's point l % 16 of each 16 (the four lanes of a point agree).
 // Directions below a point's own s are computed and not applied.
-constexpr int CU_MD = 4;
+// Blocks of 16 directions start at multiples of 16 and are subtracted one
+// by one, so that a point's d depends on its own s and k alone and not on
+// the points that share its wave.
 template <typename S> constexpr int CU_MP = 2;
-template <typename G>
-__device__ inline void catch_up(const G* col, int64_t ld, int last, int n_orb,
-                                const typename Scal<G>::S* QT, int k,
-                                const bool* on, double* dv, const int* s) {
+
+// MD blocks from direction kb on.  The entries of the next four orbitals are
+// read while the matrix cores work on these four.
+template <int MD, typename G>
+__device__ __forceinline__ void catch_up_blocks(const G* col, int64_t ld, int last,
+                                                int n_orb,
+                                                const typename Scal<G>::S* QT,
+                                                int kb, int k, double* dv,
+                                                const int* s) {
   using S = typename Scal<G>::S;
   constexpr bool CX = sizeof(S) == 16;
-  constexpr int MD = CU_MD, MP = CU_MP<S>;
+  constexpr int MP = CU_MP<S>;
   const int lane = threadIdx.x & 63, l16 = lane & 15, g4 = lane >> 4;
   const int ldq = q_ld<S>(n_orb);
-  int smin = k;
+  d4 re[MD][MP], im[CX ? MD : 1][MP];
 #pragma unroll
-  for (int j = 0; j < MP; ++j)
-    if (on[j] && dv[j] >= 0.0) smin = min(smin, s[j]);
+  for (int a = 0; a < MD; ++a)
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) smin = min(smin, __shfl_xor(smin, o, 64));
-  for (int kb = smin; kb < k; kb += 16 * MD) {
-    d4 re[MD][MP], im[CX ? MD : 1][MP];
+    for (int j = 0; j < MP; ++j) {
+      re[a][j] = d4{0, 0, 0, 0};
+      if (CX) im[a][j] = d4{0, 0, 0, 0};
+    }
+  G x[MP];
+  S q[MD];
+  // every load runs: past the last orbital or direction a valid entry is
+  // read and its factor zeroed, past the last point one that is not used
+  auto fetch = [&](int n0) {
+    const int n = min(n0 + g4, n_orb - 1);
+#pragma unroll
+    for (int j = 0; j < MP; ++j) x[j] = col[(int64_t)n * ld + min(16 * j + l16, last)];
+#pragma unroll
+    for (int a = 0; a < MD; ++a)
+      q[a] = QT[(int64_t)n * ldq + min(kb + 16 * a + l16, k - 1)];
+  };
+  fetch(0);
+  for (int n0 = 0; n0 < n_orb; n0 += 4) {
+    S xc[MP], qc[MD];
+#pragma unroll
+    for (int j = 0; j < MP; ++j) xc[j] = to_s(x[j], S{});
+#pragma unroll
+    for (int a = 0; a < MD; ++a)
+      qc[a] = n0 + g4 < n_orb && kb + 16 * a + l16 < k ? q[a] : zero_s(S{});
+    fetch(n0 + 4);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int a = 0; a < MD; ++a)
 #pragma unroll
       for (int j = 0; j < MP; ++j) {
-        re[a][j] = d4{0, 0, 0, 0};
-        if (CX) im[a][j] = d4{0, 0, 0, 0};
-      }
-    // every load runs: past the last orbital or direction a valid entry is
-    // read and its factor zeroed, past the last point one that is not used
-#pragma unroll 4
-    for (int n0 = 0; n0 < n_orb; n0 += 4) {
-      const int n = min(n0 + g4, n_orb - 1);
-      S x[MP], q[MD];
-#pragma unroll
-      for (int j = 0; j < MP; ++j)
-        x[j] = to_s(col[(int64_t)n * ld + min(16 * j + l16, last)], S{});
-#pragma unroll
-      for (int a = 0; a < MD; ++a) {
-        const int m = kb + 16 * a + l16;
-        const S v = QT[(int64_t)n * ldq + min(m, k - 1)];
-        q[a] = n0 + g4 < n_orb && m < k ? v : zero_s(S{});
-      }
-#pragma unroll
-      for (int a = 0; a < MD; ++a)
-#pragma unroll
-        for (int j = 0; j < MP; ++j) {
-          if constexpr (CX) {
-            re[a][j] = mfma(q[a].x, x[j].x, re[a][j]);
-            im[a][j] = mfma(q[a].x, x[j].y, im[a][j]);
-            re[a][j] = mfma(-q[a].y, x[j].y, re[a][j]);
-            im[a][j] = mfma(q[a].y, x[j].x, im[a][j]);
-          } else {
-            re[a][j] = mfma(q[a], x[j], re[a][j]);
-          }
+        if constexpr (CX) {
+          re[a][j] = mfma(qc[a].x, xc[j].x, re[a][j]);
+          im[a][j] = mfma(qc[a].x, xc[j].y, im[a][j]);
+          re[a][j] = mfma(-qc[a].y, xc[j].y, re[a][j]);
+          im[a][j] = mfma(qc[a].y, xc[j].x, im[a][j]);
+        } else {
+          re[a][j] = mfma(qc[a], xc[j], re[a][j]);
         }
-    }
+      }
+  }
 #pragma unroll
-    for (int j = 0; j < MP; ++j) {
+  for (int j = 0; j < MP; ++j)
+#pragma unroll
+    for (int a = 0; a < MD; ++a) {
       double sum = 0.0;
 #pragma unroll
-      for (int a = 0; a < MD; ++a)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int m = kb + 16 * a + g4 + 4 * e;
-          double v = re[a][j][e] * re[a][j][e];
-          if (CX) v += im[a][j][e] * im[a][j][e];
-          if (m >= s[j] && m < k) sum += v;
-        }
+      for (int e = 0; e < 4; ++e) {
+        const int m = kb + 16 * a + g4 + 4 * e;
+        double v = re[a][j][e] * re[a][j][e];
+        if (CX) v += im[a][j][e] * im[a][j][e];
+        if (m >= s[j] && m < k) sum += v;
+      }
       sum += __shfl_xor(sum, 16, 64);
       sum += __shfl_xor(sum, 32, 64);
       if (dv[j] >= 0.0) dv[j] = fmax(dv[j] - sum, 0.0);
     }
-  }
+}
+
+template <typename G>
+__device__ inline void catch_up(const G* col, int64_t ld, int last, int n_orb,
+                                const typename Scal<G>::S* QT, int k,
+                                const bool* on, double* dv, const int* s) {
+  int smin = k;
+#pragma unroll
+  for (int j = 0; j < CU_MP<typename Scal<G>::S>; ++j)
+    if (on[j] && dv[j] >= 0.0) smin = min(smin, s[j]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) smin = min(smin, __shfl_xor(smin, o, 64));
+  if (smin >= k) return;
+  int kb = smin & ~15;
+  for (; k - kb > 48; kb += 64) catch_up_blocks<4, G>(col, ld, last, n_orb, QT, kb, k, dv, s);
+  if (k - kb > 32) catch_up_blocks<3, G>(col, ld, last, n_orb, QT, kb, k, dv, s);
+  else if (k - kb > 16) catch_up_blocks<2, G>(col, ld, last, n_orb, QT, kb, k, dv, s);
+  else if (k - kb > 0) catch_up_blocks<1, G>(col, ld, last, n_orb, QT, kb, k, dv, s);
 }
 
 // A refresh's histogram of d.  When LZ_FRESH directions or more have come
@@ -826,15 +850,24 @@ static size_t lazy_bytes(int n_orb, int64_t ng, size_t point) {
          point * cap * (size_t)n_orb;
 }
 
-// The lazy selection pays where a full downdate (at 5.6 TB/s, 192 MB take
-// 34 us) costs more than its launches (three a step that return at once) and
-// refreshes.  Measured, whole call, every point each step before -> now:
-// 120^3 with 256 real FP32 orbitals (1.8 GB) 97.0 -> 31.4 ms, 96^3 with 128
-// (453 MB) 15.8 -> 7.5 ms, 80^3 with 96 (197 MB) 6.0 -> 4.4 ms, complex FP64
-// 80^3 with 96 (786 MB) 17.7 -> 7.8 ms; below the line the pick and the
-// downdate alone changed: 80^3 with 60 (123 MB) 3.1 -> 2.8 ms, 64^3 with 64
-// 2.8 -> 2.1 ms, 48^3 with 32 1.23 -> 0.53 ms.
-constexpr double LZ_MIN_BYTES = 192e6;
+// The lazy selection replaces n_orb passes over the grids by launches (three a
+// step that return at once, 15 us) and a few refreshes.  It pays where a
+// pass takes more than the launches (at 5.6 TB/s 192 MB take 34 us; complex
+// grids, whose catch-ups cost twice the arithmetic per byte, 256 MB) and all
+// passes together more than the refreshes (11 GB: 2 ms).  Measured, whole
+// call, every point each step -> lazy, localized orbitals mixed by a rotation
+// / random ones: 120^3 real FP32 with 200 (1.4 GB) 59.3 -> 17.2 / with 220 72.0
+// -> 24.8 ms, 96^3 with 128 (453 MB) 13.6 -> 6.2 / 13.8 -> 7.7, 96^3 with 60
+// (212 MB, 12.7 GB in all) 3.2 -> 2.8 / 3.6 -> 2.9, 80^3 with 96 (197 MB) 4.8 ->
+// 4.0; complex FP32 96^3 with 40 (283 MB, 11.3 GB in all) 2.6 -> 2.1, 96^3 with
+// 64 - / 7.1 -> 6.6, 120^3 with 30 (415 MB, 12.4 GB in all) - / 3.5 -> 3.7;
+// complex FP64 120^3 with 30 (829 MB) 6.2 -> 3.1.  Beyond the line: complex FP32
+// 64^3 with 100 (210 MB) - / 5.3 -> 5.8, 80^3 with 60 (246 MB) - / 3.6 -> 4.0,
+// 120^3 with 16 (221 MB, 3.5 GB in all) - / 1.1 -> 2.2; real FP32 120^3 with 28
+// (193 MB, 5.4 GB in all) - / 1.7 -> 2.1.
+static bool lazy_pays(bool complex_grids, double n_orb, double bytes) {
+  return bytes >= (complex_grids ? 256e6 : 192e6) && n_orb * bytes >= 11e9;
+}
 
 template <typename G>
 static hipError_t scdm_t(const G* psi, int n_orb, int64_t ng, double* d,
@@ -852,8 +885,9 @@ static hipError_t scdm_t(const G* psi, int n_orb, int64_t ng, double* d,
   // one vector of points per thread where the partials allow
   const int64_t per_block = (int64_t)AM_NT * (vec ? VW : 1);
   const int parts = (int)std::min<int64_t>(AM_BLOCKS, (ng + per_block - 1) / per_block);
-  const bool lazy = ng % VW == 0 && n_orb >= 16 &&
-                    (double)n_orb * (double)ng * sizeof(G) >= LZ_MIN_BYTES &&
+  const bool lazy = ng % VW == 0 &&
+                    lazy_pays(sizeof(S) == 16, n_orb,
+                              (double)n_orb * (double)ng * sizeof(G)) &&
                     (int64_t)lazy_bytes(n_orb, ng, sizeof(G)) <= buf_bytes;
   char* b = static_cast<char*>(buf);
   LazyCtl* ctl = reinterpret_cast<LazyCtl*>(b);
