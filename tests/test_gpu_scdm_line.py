@@ -1,6 +1,6 @@
 """SCDM on both sides of the line between downdating every point and the lazy
-selection, in every grid form.  The picks are checked as in
-test_gpu_scdm_lazy."""
+selection, in every grid form; and an input that makes the lazy selection give
+up.  The picks are checked as in test_gpu_scdm_lazy."""
 import numpy as np
 import pytest
 
@@ -41,3 +41,23 @@ def test_uniform_density():
     c[np.arange(40), np.random.default_rng(76).permutation(miller.shape[0])[:40]] = 1.0
     points, _ = run(c, miller, lace.LACE_FP64)
     check_greedy(c, miller, points, 1e-12)
+
+
+@pytest.mark.parametrize("prec,n_orb", [("fp64g", 55), ("fp64", 39)])
+def test_gives_up_after_refreshes_without_a_pick(prec, n_orb):
+    """Two orbitals hold almost all of the density, everywhere: their picks
+    leave nothing of the points that each following refresh selects by their
+    old values, and there are more such refreshes (the same selection in numpy
+    counts 9) than are allowed before every point is updated.  The other
+    orbitals are picked after that."""
+    miller = synth.miller_sphere(L, 40.0)
+    c = 1e-4 * synth.gaussian_orbitals(miller, L, n_orb, (n_orb + 1) // 2,
+                                       synth.rng_for(77))
+    # f(x) f(y) f(z) with f = 1.2 + cos, of one and two periods: each density
+    # over 20 octaves
+    for k, amp in ((1, 1.0), (2, 1e-2)):
+        w = {0: 1.2, k: 0.5, -k: 0.5}
+        c[k - 1] = [amp * np.prod([w.get(int(v), 0.0) for v in m]) for m in miller]
+    p = lace.LACE_FP64_GAMMA if prec.endswith("g") else lace.LACE_FP64
+    points, _ = run(c, miller, p)
+    check_greedy(c, miller, points, 1e-13)
