@@ -442,13 +442,20 @@ __global__ __launch_bounds__(256) void k_ip_narrow(const double2* A, int64_t lda
     double2 ya[2][4], yb[NBT][4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const bool in = k0 + 4 * g + s < ke;
 #pragma unroll
       for (int p = 0; p < 2; ++p) ya[p][s] = xa[p][s];
 #pragma unroll
-      for (int q = 0; q < NBT; ++q)
-        yb[q][s] = make_double2(in ? xb[q][s].x : 0.0, in ? xb[q][s].y : 0.0);
+      for (int q = 0; q < NBT; ++q) yb[q][s] = xb[q][s];
     }
+    if (k0 + 16 > ke)   // both factors: infinity times a zero would be a NaN
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (k0 + 4 * g + s >= ke) {
+#pragma unroll
+          for (int p = 0; p < 2; ++p) ya[p][s] = make_double2(0.0, 0.0);
+#pragma unroll
+          for (int q = 0; q < NBT; ++q) yb[q][s] = make_double2(0.0, 0.0);
+        }
     if (k0 + NR_K < ke) fetch(k0 + NR_K);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -721,7 +728,7 @@ __global__ __launch_bounds__(256) void k_gemm_tall(const double2* X,
 // wave takes 32 points m x 16 NBT columns b, D = Z^T X with the rows of D
 // along b, so that a store writes 16 consecutive points (256 bytes) of a
 // column; Z stays in the caches.  Every load of four k steps is issued
-// before their MFMAs; past the last k a valid entry is read and Z's zeroed.
+// before their MFMAs; past the last k valid entries are read and zeroed.
 template <int NBT>
 __global__ __launch_bounds__(256) void k_tall_narrow(const double2* X, int64_t ldx,
                                                      int64_t M, int nk,
@@ -755,12 +762,20 @@ __global__ __launch_bounds__(256) void k_tall_narrow(const double2* X, int64_t l
 #pragma unroll
       for (int q = 0; q < NBT; ++q) z[q][s] = pz[q][(int64_t)kc * nb];
     }
+    if (k0 + 16 > nk)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (k0 + 4 * s + g >= nk) {
+#pragma unroll
+          for (int p = 0; p < 2; ++p) x[p][s] = make_double2(0.0, 0.0);
+#pragma unroll
+          for (int q = 0; q < NBT; ++q) z[q][s] = make_double2(0.0, 0.0);
+        }
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const bool in = k0 + 4 * s + g < nk;
 #pragma unroll
       for (int q = 0; q < NBT; ++q) {
-        const double zr = in ? z[q][s].x : 0.0, zi = in ? z[q][s].y : 0.0;
+        const double zr = z[q][s].x, zi = z[q][s].y;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
           re[q][p] = mfma(zr, x[p][s].x, re[q][p]);
