@@ -408,6 +408,7 @@ __global__ __launch_bounds__(256) void k_ip_narrow(const double2* A, int64_t lda
   const int a0 = blockIdx.x * NR_A;
   const int64_t kb = blockIdx.y * kchunk;
   const int64_t ke = kb + kchunk < K ? kb + kchunk : K;
+  const int b0 = blockIdx.z * 16 * NBT;   // first column of this group
   // rows past the end repeat the last one; their results are not stored
   const double2* pa[2];
   const double2* pb[NBT];
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(256) void k_ip_narrow(const double2* A, int64_t lda
   for (int p = 0; p < 2; ++p)
     pa[p] = A + (int64_t)min(a0 + 16 * p + l16, na - 1) * lda;
 #pragma unroll
-  for (int q = 0; q < NBT; ++q) pb[q] = B + (int64_t)min(16 * q + l16, nb - 1) * ldb;
+  for (int q = 0; q < NBT; ++q) pb[q] = B + (int64_t)min(b0 + 16 * q + l16, nb - 1) * ldb;
   d4 re[2][NBT], im[2][NBT];
 #pragma unroll
   for (int p = 0; p < 2; ++p)
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(256) void k_ip_narrow(const double2* A, int64_t lda
           r += red[v][lane][i];
           c += red[v][lane][i + 4];
         }
-        const int a = a0 + 16 * p + g + 4 * e, b = 16 * q + l16;
+        const int a = a0 + 16 * p + g + 4 * e, b = b0 + 16 * q + l16;
         if (a < na && b < nb) {
           out[2 * ((int64_t)a * nb + b)] = r;
           out[2 * ((int64_t)a * nb + b) + 1] = c;
@@ -526,6 +527,21 @@ static SplitPlan split_plan(int na, int nb, int64_t K) {
   sp.nsplit = (int)((K + chunk - 1) / chunk);
   if (sp.nsplit < 1) sp.nsplit = 1;
   return sp;
+}
+
+// 17 to 32 columns in the narrow forms: one group of 32, which reads the
+// n x n_pw side once, or two groups of 16 in workgroups of their own, each
+// with half the chain per k, where that side (300 MB and below: the 256 MB
+// cache and a little) is read again from the cache, or where one group has
+// too few workgroups (n_pw / 128) for the chip.  Measured, whole application
+// to 17 functions, 64 x 64 tiles / one group / two: 256 orbitals x 6000 74 / 77
+// / 51 us, 1500 x 1500 258 / 280 / 155, 1500 x 12000 (288 MB) 393 / 404 / 288, 600
+// x 25000 (240 MB) 331 / 236 / 214, 131 x 80000 266 / 184 / 162; beyond the
+// line 256 x 80000 (328 MB) 400 / 296 / 337, 1500 x 25000 768 / 575 / 614, 256 x
+// 160000 753 / 550 / 685.
+static int column_groups(int n, int nb, int64_t n_pw) {
+  if (nb <= 16) return 1;
+  return 16.0 * n * (double)n_pw < 300e6 || n_pw <= 16384 ? 2 : 1;
 }
 
 // The narrow form's split: about 1024 workgroups, whole rounds of k.
@@ -602,11 +618,12 @@ hipError_t launch_gemm_ip_c128(const void* A, int64_t lda, int na,
   // than half and the staged tiles read A and B less often.
   const SplitPlan sp = narrow_plan(na, K);
   if ((int64_t)sp.nsplit * na * nb * 16 > part_bytes) return hipErrorInvalidValue;
-  const dim3 grid((na + NR_A - 1) / NR_A, sp.nsplit);
   const double2* a = static_cast<const double2*>(A);
   const double2* b = static_cast<const double2*>(B);
   double* p = static_cast<double*>(part);
-  if (nb <= 16)
+  const int groups = column_groups(na, nb, K);
+  const dim3 grid((na + NR_A - 1) / NR_A, sp.nsplit, groups);
+  if (nb <= 16 * groups)
     LACE_LAUNCH(k_ip_narrow<1>, grid, dim3(256), 0, st, a, lda, na, b, ldb, nb, K,
                 sp.kchunk, p);
   else
@@ -738,12 +755,13 @@ __global__ __launch_bounds__(256) void k_tall_narrow(const double2* X, int64_t l
   const int l16 = lane % 16, g = lane / 16;
   const int64_t m0 = ((int64_t)blockIdx.x * 4 + w) * 32;
   if (m0 >= M) return;
+  const int b0 = blockIdx.y * 16 * NBT;   // first column of this group
   const double2* px[2];
   const double2* pz[NBT];
 #pragma unroll
   for (int p = 0; p < 2; ++p) px[p] = X + (m0 + 16 * p + l16 < M ? m0 + 16 * p + l16 : M - 1);
 #pragma unroll
-  for (int q = 0; q < NBT; ++q) pz[q] = Z + min(16 * q + l16, nb - 1);
+  for (int q = 0; q < NBT; ++q) pz[q] = Z + min(b0 + 16 * q + l16, nb - 1);
   d4 re[NBT][2], im[NBT][2];
 #pragma unroll
   for (int q = 0; q < NBT; ++q)
@@ -792,7 +810,7 @@ __global__ __launch_bounds__(256) void k_tall_narrow(const double2* X, int64_t l
     for (int p = 0; p < 2; ++p)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int b = 16 * q + g + 4 * e;
+        const int b = b0 + 16 * q + g + 4 * e;
         const int64_t m = m0 + 16 * p + l16;
         if (b < nb && m < M) Y[(int64_t)b * ldy + m] = make_double2(re[q][p][e], im[q][p][e]);
       }
@@ -807,12 +825,12 @@ hipError_t launch_gemm_tall(const void* X, int64_t ldx, int64_t M, int nk,
     const double2* x = static_cast<const double2*>(X);
     const double2* z = static_cast<const double2*>(Z);
     double2* y = static_cast<double2*>(Y);
-    if (nb <= 16)
-      LACE_LAUNCH(k_tall_narrow<1>, dim3((unsigned)nblk), dim3(256), 0, st, x, ldx, M,
-                  nk, z, nb, y, ldy);
+    const int groups = column_groups(nk, nb, M);
+    const dim3 grid((unsigned)nblk, groups);
+    if (nb <= 16 * groups)
+      LACE_LAUNCH(k_tall_narrow<1>, grid, dim3(256), 0, st, x, ldx, M, nk, z, nb, y, ldy);
     else
-      LACE_LAUNCH(k_tall_narrow<2>, dim3((unsigned)nblk), dim3(256), 0, st, x, ldx, M,
-                  nk, z, nb, y, ldy);
+      LACE_LAUNCH(k_tall_narrow<2>, grid, dim3(256), 0, st, x, ldx, M, nk, z, nb, y, ldy);
     return hipGetLastError();
   }
   const int nbb = (nb + 63) / 64;
