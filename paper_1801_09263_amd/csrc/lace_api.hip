@@ -582,8 +582,6 @@ static void batch_bytes(const lace_plan* p, const CellDev& c, const BatchDev& bt
   out[2] = bt.n * U + orbs_c * G;
 }
 
-// One batch of the pair pipeline (pairs, or packed slots for Gamma plans).
-// `lane` picks the pair buffer and the energy partials (0 or 1).
 // Slot capacity of a batch with at most ppb pairs.
 static int slot_cap(const lace_plan* p, int ppb) {
   return p->gamma ? (ppb + 1) / 2 : ppb;
@@ -599,26 +597,39 @@ static int batch_slots(const lace_plan* p, int n_orb, int ppb) {
 
 // Batches per group, 0 for batch by batch.  A group runs the passes A and B
 // of all its batches in one launch each, on one stream, in the pair buffers
-// of both lanes.  It replaces the two-stream pipeline (two) while the pair
-// buffers of one batch stay below a size, from which on the launches of
-// single batches fill the chip and the overlap of two streams gains more.
-// Measured, whole exchange, two streams -> groups (bytes of one batch's
-// buffers), real FP32: 12^3 with 2 orbitals 266 -> 88 us, 24^3 / 16 593 ->
-// 190 us, 48^3 / 32 (14 MB) 1134 -> 768 us, 64^3 / 64 (34 MB) 4.55 -> 4.16
-// ms, 80^3 / 96 (66 MB) 16.2 -> 15.3 ms, 96^3 / 128 (113 MB) 25.8 -> 24.4
-// ms; with larger batches 80^3 / 96 (131 MB) 14.4 -> 15.3 ms, 120^3 / 256
-// (221 and 442 MB) 317 -> 328 and 314 -> 322 ms.  FP64: 48^3 / 16 complex (28
-// MB) 798 -> 704 us, 32 real (28 MB) 1335 -> 1155 us, 24 complex (42 MB) 1427
-// -> 1511 us, 64^3 (67 MB) 5.25 -> 5.28 ms.  On one stream (a batched call's
-// jobs) groups replace single batches of any size: 8 cells 84.2 -> 79.1 ms.
+// of both lanes.
+//
+// On one stream (a batched or captured call's jobs) groups replace single
+// batches wherever their kernels exist: half planes, or whole planes that fit
+// the LDS, FP32 of any size and FP64 up to 48^3.  FP64 above, the pencil
+// schedule and profiled calls run batch by batch.  8 cells 84.2 -> 79.1 ms.
+//
+// They replace the two-stream pipeline (two) while the pair buffers of one
+// batch stay below a size, from which on the launches of single batches fill
+// the chip and the overlap of two streams gains more.  Measured, whole
+// exchange, two streams -> groups (bytes of one batch's buffers):
+//   real FP32    32^3 / 130 orbitals (17 MB) 4.67 -> 3.82 ms, 64^3 / 64 (34 MB)
+//                4.43 -> 4.10, 80^3 / 40 (82 MB) 3.72 -> 3.75, 96^3 / 28 (99 MB)
+//                3.08 -> 3.04, 96^3 / 128 (113 MB) 25.8 -> 24.4; beyond 80^3 /
+//                96 (131 MB) 14.4 -> 15.3, 120^3 / 256 (221 MB) 317 -> 328
+//   complex FP32 24^3 / 64 (7 MB) 2.39 -> 1.93, 64^3 / 80 (67 MB) 15.6 -> 14.7,
+//                80^3 / 22 (90 MB) 2.52 -> 2.51, 96^3 / 16 (113 MB) 2.26 -> 2.25,
+//                120^3 / 8 (110 MB) 1.49 -> 1.50
+//   FP64         complex 48^3 / 16 (28 MB) 749 -> 678 us, / 24 (42 MB) 1427 ->
+//                1511, real 48^3 / 36 (32 MB) 1.54 -> 1.38 ms
+// A group of two batches (complex: of three as well) of more than 32 MB joins
+// too little: complex 48^3 / 64 with 64 pairs (57 MB, two) 4.72 -> 5.03 ms, 64^3 /
+// 40 with 34 (71 MB, three) 3.60 -> 3.78; real 48^3 / 128 with 128 (57 MB, two)
+// 8.74 -> 8.98, but 48^3 / 80 (35 MB, three) 4.20 -> 3.87; complex 32^3 / 100 with
+// 64 (17 MB, two) 5.11 -> 4.72.
 static int group_batches(const lace_plan* p, const CellDev& c, int n_orb, int ppb,
                          bool two) {
   if (c.use_plane == 0 || (c.use_plane == 1 && !plane_fits(c.n, p->fp64))) return 0;
   if (p->fp64 && c.n > 48) return 0;   // no group kernels there
   const int slots = batch_slots(p, n_orb, ppb);
-  const double bytes = (double)slots * (double)c.ng * (double)grid_bytes(p);
-  if (two && bytes > (p->fp64 ? 32e6 : 120e6)) return 0;
   const int g = 2 * SMAX / slots;
+  const double bytes = (double)slots * (double)c.ng * (double)grid_bytes(p);
+  if (two && bytes > (p->fp64 || g < (p->gamma ? 3 : 4) ? 32e6 : 120e6)) return 0;
   return g >= 2 ? g : 0;
 }
 
