@@ -242,47 +242,3 @@ hipError_t launch_scdm(bool fp64, bool real, const void* psi, int n_orb,
     if (lace_resolve_err_ != hipSuccess) return lace_resolve_err_; \
     hipLaunchKernelGGL(K, __VA_ARGS__);                            \
   } while (0)
-
-// The host layer also builds as plain C++ without the kernels (its thread
-// and address checks): launchers without a stand-in of their own there
-// write the whole extent of their outputs.
-#if !defined(__HIP__)
-#include <cstring>
-namespace lace {
-inline int64_t polar_state_bytes() { return 512; }
-inline hipError_t launch_polar(const void*, bool, int n, void* ya, void* yb,
-                               void* b, void* state, void* U, double* resid,
-                               hipStream_t) {
-  for (void* p : {ya, yb, b, U}) std::memset(p, 0x3c, 16 * (size_t)n * n);
-  std::memset(state, 0, (size_t)polar_state_bytes());
-  if (resid) *resid = 0.0;
-  return hipSuccess;
-}
-inline hipError_t launch_batch_group(const CellDev& c, bool fp64, bool real,
-                                     const BatchDev* bt, int nb, int cap,
-                                     const void* psi, void* w, void* tmp,
-                                     double* epart, hipStream_t st) {
-  const int64_t g = c.ng * (fp64 ? 16 : 8);
-  for (int b = 0; b < nb; ++b) {
-    char* t = static_cast<char*>(tmp) + (int64_t)b * cap * g;
-    double* e = epart + (int64_t)b * cap * energy_tiles(c.n, fp64);
-    const hipError_t r =
-        real ? launch_quad_batch(c, fp64, bt + b, cap, psi, w, t, e, st, nullptr)
-             : launch_pair_batch(c, fp64, bt + b, cap, psi, w, t, e, st, nullptr);
-    if (r != hipSuccess) return r;
-  }
-  return hipSuccess;
-}
-inline hipError_t launch_scdm(bool, bool, const void* psi, int n_orb, int64_t ng,
-                              double* d, void* scratch, void* buf,
-                              int64_t buf_bytes, int32_t* points, void* Y,
-                              hipStream_t) {
-  std::memset(d, static_cast<const char*>(psi)[0] & 1, sizeof(double) * (size_t)ng);
-  std::memset(scratch, 0x3c, (size_t)scdm_scratch_bytes(n_orb));
-  std::memset(buf, 0x3c, (size_t)buf_bytes);
-  for (int k = 0; k < n_orb; ++k) points[k] = k;
-  std::memset(Y, 0x3c, 16 * (size_t)n_orb * n_orb);
-  return hipSuccess;
-}
-}  // namespace lace
-#endif

@@ -26,7 +26,12 @@ bool grid_supported(int n) {
   return false;
 }
 bool plane_fits(int n, bool fp64) { return (int64_t)n * n * gb(fp64) <= 150 * 1024; }
-int64_t energy_tiles(int n, bool fp64) { return (int64_t)n * n / (256 / gb(fp64)) + 1; }
+int64_t energy_tiles(int n, bool fp64) {   // of the smallest tile
+  int tx = ztile_points(n, fp64, 0);
+  for (int z : {1, 2})
+    if (ztile_points(n, fp64, z) < tx) tx = ztile_points(n, fp64, z);
+  return (int64_t)n * n / tx;
+}
 int64_t gemm_ip_part_bytes(int na, int nb, int64_t K, bool complex_out) {
   return 2 * (int64_t)na * nb * (complex_out ? 16 : 8) + (K & 7);
 }
@@ -49,6 +54,9 @@ hipError_t launch_grid_to_pw(const CellDev& c, bool fp64, void* w, int n_orb,
   touch(w_pw, c.n_pw * n_orb * 16);
   return hipSuccess;
 }
+static int64_t cell_tiles(const CellDev& c, bool fp64) {   // of the selected tile
+  return (int64_t)c.n * c.n / ztile_points(c.n, fp64, c.ztile);
+}
 static hipError_t batch(const CellDev& c, bool fp64, bool real,
                         const BatchDev* bt, int cap, const void* psi, void* w,
                         void* tmp, double* epart, hipEvent_t* ev) {
@@ -65,7 +73,7 @@ static hipError_t batch(const CellDev& c, bool fp64, bool real,
       touch(static_cast<char*>(w) + o * g, g);
     }
   touch(tmp, cap * c.ng * gb(fp64));
-  touch(epart, cap * energy_tiles(c.n, fp64) * (int64_t)sizeof(double));
+  touch(epart, cap * cell_tiles(c, fp64) * (int64_t)sizeof(double));
   return hipSuccess;
 }
 hipError_t launch_pair_batch(const CellDev& c, bool fp64, const BatchDev* bt,
@@ -180,15 +188,14 @@ hipError_t launch_trace_re(const void* M, int n, double factor, double* out,
   *out = factor;
   return hipSuccess;
 }
-hipError_t launch_polar_elem(int, const void* in, int n, const double*, void* out,
-                             hipStream_t) {
-  sink = peek(in, (int64_t)n * n * 16);
-  touch(out, (int64_t)n * n * 16);
-  return hipSuccess;
-}
-hipError_t launch_polar_norm(int, const void* B, int n, double* out, hipStream_t) {
-  sink = peek(B, (int64_t)n * n * 16);
-  *out = 1.0;
+int64_t polar_state_bytes() { return 512; }
+hipError_t launch_polar(const void* Y0, bool, int n, void* ya, void* yb, void* b,
+                        void* state, void* U, double* resid, hipStream_t) {
+  const int64_t bytes = (int64_t)n * n * 16;
+  sink = peek(Y0, bytes);
+  for (void* p : {ya, yb, b, U}) touch(p, bytes);
+  touch(state, polar_state_bytes());
+  if (resid) *resid = 0.0;
   return hipSuccess;
 }
 int64_t sched_scratch_bytes(int n_orb) { return 4096 + 64 * (int64_t)n_orb * n_orb; }
@@ -239,13 +246,34 @@ hipError_t launch_kept_pairs(const double* s, int n, double, int32_t* cnt,
 }
 
 hipError_t launch_scdm(bool fp64, bool real, const void* psi, int n_orb,
-                       int64_t ng, double* d, void* scratch, int32_t* points,
-                       void* Y, hipStream_t) {
-  sink = peek(psi, n_orb * ng * gb(fp64) / (real ? 2 : 1));
+                       int64_t ng, double* d, void* scratch, void* buf,
+                       int64_t buf_bytes, int32_t* points, void* Y, hipStream_t) {
+  const int64_t bytes = n_orb * ng * gb(fp64) / (real ? 2 : 1);
+  touch(buf, buf_bytes);
+  sink = peek(psi, bytes);
+  // apart from the grids, which the caller still reads
+  const char* a = static_cast<const char*>(psi);
+  const char* b = static_cast<const char*>(buf);
+  if (b < a + bytes && a < b + buf_bytes) return hipErrorInvalidValue;
   touch(d, ng * (int64_t)sizeof(double));
   touch(scratch, scdm_scratch_bytes(n_orb));
   for (int k = 0; k < n_orb; ++k) points[k] = k;
   touch(Y, (int64_t)n_orb * n_orb * 16);
+  return hipSuccess;
+}
+// The group's batches have consecutive slots in the pair buffers and, at the
+// tile count of the selected z tile, in the energy cells.
+hipError_t launch_batch_group(const CellDev& c, bool fp64, bool real,
+                              const BatchDev* bt, int nb, int cap,
+                              const void* psi, void* w, void* tmp, double* epart,
+                              hipStream_t) {
+  if (nb < 1 || nb * cap > 2 * SMAX || c.use_plane == 0) return hipErrorInvalidValue;
+  for (int b = 0; b < nb; ++b) {
+    char* t = static_cast<char*>(tmp) + (int64_t)b * cap * c.ng * gb(fp64);
+    double* e = epart + (int64_t)b * cap * cell_tiles(c, fp64);
+    const hipError_t r = batch(c, fp64, real, bt + b, cap, psi, w, t, e, nullptr);
+    if (r != hipSuccess) return r;
+  }
   return hipSuccess;
 }
 
