@@ -856,7 +856,7 @@ static size_t lazy_bytes(int n_orb, int64_t ng, size_t point) {
 // grids, whose catch-ups cost twice the arithmetic per byte, 256 MB) and all
 // passes together more than the refreshes (11 GB: 2 ms).  Measured, whole
 // call, every point each step -> lazy, localized orbitals mixed by a rotation
-// / random ones: 120^3 real FP32 with 200 (1.4 GB) 59.3 -> 17.2 / with 220 72.0
+// / random ones: 120^3 real FP32 with 200 (1.4 GB) 59.3 -> 16.0 / with 220 72.0
 // -> 24.8 ms, 96^3 with 128 (453 MB) 13.6 -> 6.2 / 13.8 -> 7.7, 96^3 with 60
 // (212 MB, 12.7 GB in all) 3.2 -> 2.8 / 3.6 -> 2.9, 80^3 with 96 (197 MB) 4.8 ->
 // 4.0; complex FP32 96^3 with 40 (283 MB, 11.3 GB in all) 2.6 -> 2.1, 96^3 with
@@ -905,12 +905,13 @@ static hipError_t scdm_t(const G* psi, int n_orb, int64_t ng, double* d,
     LACE_LAUNCH((k_scdm_density<G, 1>), dim3(parts), dim3(AM_NT), 0, st, psi,
                 n_orb, ng, d, missed, points, pv, pi);
   hipError_t e = hipGetLastError();
-  // Threads of the pick: Gram-Schmidt against 256 directions is bound by how
+  // Threads of the pick: Gram-Schmidt against many directions is bound by how
   // much one CU has in flight, a few directions by the barriers of many
-  // waves.  Measured, whole call, 256 / 512 / 1024 threads: 64^3 with 64
-  // real orbitals 2.05 / 2.08 / 2.9 ms, 96^3 with 128 7.96 / 7.49 / 7.64,
-  // 120^3 with 256 38.6 / 32.5 / 31.4.
-  const int nt = n_orb <= 64 ? 256 : n_orb <= 192 ? 512 : 1024;
+  // waves.  Measured, whole call, 256 / 512 / 1024 threads: complex FP64 32^3
+  // with 64 orbitals 1.33 / 1.43 / 1.66 ms, real FP32 48^3 with 32 526 / 526 /
+  // 634 us, complex FP32 48^3 with 200 11.8 / 10.7 / 11.8 ms, complex FP64 24^3
+  // with 300 23.5 / 17.8 / 18.9, 450 - / 46.3 / 49.1, 700 - / 155.6 / 152.3.
+  const int nt = n_orb <= 64 ? 256 : n_orb <= 512 ? 512 : 1024;
   const size_t dir_lds = 2 * qlds + 16 * (size_t)nt;
   auto eager_pick = [&](int k) -> hipError_t {
     if (nt == 256)
