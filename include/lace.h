@@ -219,8 +219,9 @@ int lace_align(lace_plan* plan, int cell, const void* psi_new,
  *   points  device int32 [n_orb] (may be NULL): the picks in order, as flat
  *           grid indices (z n + y) n + x.
  *   resid   device double (may be NULL): ||U^H U - I||_F / sqrt(n_orb).
- * n_orb <= 3072.  Workspace of n_orb.  Asynchronous (n_orb steps, each a
- * pass over the orbital grids).  Errors: EINVAL, ENOMEM, EHIP. */
+ * n_orb <= 3072.  Workspace of n_orb.  Asynchronous (n_orb steps; each is a
+ * pass over the orbital grids, on large grids over the points that can be
+ * picked next).  Errors: EINVAL, ENOMEM, EHIP. */
 int lace_scdm(lace_plan* plan, int cell, const void* psi_g, int n_orb,
               void* phi_g, int32_t* points, double* resid, void* ws,
               size_t ws_bytes, lace_stream_t stream);

@@ -388,9 +388,9 @@ static hipError_t launch_splitk_reduce(const double* part, int64_t nel,
 // do), the next block's loads issued before this block's MFMAs.  The four
 // waves of a workgroup take blocks of 16 k in turn and add their tiles in
 // wave order in LDS, so the partials stay few.
-// 131 orbitals x 6 functions x 167,037: the whole application 488 -> 212 us
+// 131 orbitals x 6 functions x 167,037: the whole application 488 -> 204-209 us
 // (this, its reduction and the tall product below; xi, 350 MB, is read twice:
-// 3.3 TB/s).
+// 3.4 TB/s).
 // ------------------------------------------------------------------
 constexpr int NR_A = 32;        // rows a of a workgroup
 constexpr int NR_B = 32;        // the most columns b
@@ -611,11 +611,11 @@ hipError_t launch_gemm_ip_c128(const void* A, int64_t lda, int na,
   if (nb > NR_B)
     return gemm_ip<0>(A, lda, na, B, ldb, nb, K, scale,
                       static_cast<double*>(out), part, part_bytes, st);
-  // up to 32 columns.  A whole application (64 x 64 tiles -> narrow): 64
-  // orbitals of 64^3 x 1 / 17 / 32 functions 80 / 84 / 88 -> 39 / 74 / 80 us,
-  // 131 of 96^3 x 6 / 16 / 32 488 / 491 / 502 -> 212 / 250 / 324 us, 256 of
-  // 120^3 x 4 / 32 683 / 700 -> 325 / 473 us; from 33 on the padding is less
-  // than half and the staged tiles read A and B less often.
+  // up to 32 columns.  A whole application (64 x 64 tiles -> narrow), in
+  // orbitals x functions x plane waves: 64 x 1 / 17 / 32 x 49,000 73 / 79 / 83 ->
+  // 39 / 62 / 67 us, 131 x 6 / 16 / 32 x 167,000 513 / 527 / 549 -> 204 / 247 / 369
+  // us, 256 x 4 / 32 x 157,000 732 / 780 -> 345 / 542 us; from 33 on the padding is
+  // less than half and the staged tiles read A and B less often.
   const SplitPlan sp = narrow_plan(na, K);
   if ((int64_t)sp.nsplit * na * nb * 16 > part_bytes) return hipErrorInvalidValue;
   const double2* a = static_cast<const double2*>(A);
@@ -883,14 +883,13 @@ hipError_t launch_neg_sym(const void* M, int n, int mode, void* A,
 }
 
 // ------------------------------------------------------------------
-// Right-looking Cholesky A = L L^H in one workgroup (n <= a few thousand).
-// A is row-major complex128, overwritten by L (strict upper zeroed).
-// ------------------------------------------------------------------
-// Blocked right-looking Cholesky, panels of CB columns: factor the diagonal
-// block in LDS (one workgroup), solve the panel below it (one thread per
-// row), subtract the panel's outer product from the trailing matrix (an
-// MFMA GEMM into tmp, then a lower-triangle update).  The first failing
-// pivot is kept in info; later blocks see it and do nothing.
+// Blocked right-looking Cholesky A = L L^H; A is row-major complex128,
+// overwritten by L (strict upper zeroed).  Panels of CB columns: factor the
+// diagonal block in the registers of one workgroup, solve the panel below it
+// (64 rows a workgroup, eight lanes a row), subtract the panel's outer product
+// from the trailing matrix (an MFMA GEMM into tmp, then a lower-triangle
+// update).  The first failing pivot is kept in info; later blocks see it and
+// do nothing.
 constexpr int CB = 64;
 
 // The diagonal block in registers: thread (ti, tj) of 16 x 16 holds the

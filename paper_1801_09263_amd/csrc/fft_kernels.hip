@@ -982,11 +982,12 @@ __global__ void k_gather(const C<T>* w, int64_t gs, const int32_t* gidx,
 template <typename T, int N> struct Cfg {
   // plane pass: whole N x N plane in LDS
   static constexpr bool plane = (int64_t)N * N * sizeof(C<T>) <= 150 * 1024;
-  // Threads: a stage of a length-48 plane has 192 or 576 butterflies, of a
-  // length-32 one 128 or 256; more threads than that only add waves to every
-  // barrier.  Measured, whole exchange, 1024 -> 256 threads: 48^3 complex
-  // FP32 with 32 orbitals 1431 -> 1299 us, 32^3 real FP32 with 20 265 -> 254;
-  // 24^3 and below and 64^3 with 512 were up to 15% slower.
+  // Threads, chosen by measurement size by size, not by a rule.  256 for FP32
+  // 32^3 and 48^3 (a stage has 128 to 576 butterflies; more threads only add
+  // waves to every barrier): whole exchange, 1024 -> 256 threads, 48^3 complex
+  // FP32 with 32 orbitals 1431 -> 1299 us, 32^3 real FP32 with 20 265 -> 254.  24^3
+  // and below have fewer butterflies still and were up to 15% slower with 256,
+  // as 64^3 with 512.  FP64 was not varied.
   static constexpr int NT_PLANE = sizeof(T) == 4 ? (N == 32 || N == 48 ? 256 : 1024) : 512;
   // y/z pencils: TX columns (>= 128 bytes of x per row when N allows)
   static constexpr int TX0 = sizeof(T) == 4 ? 16 : 8;
@@ -1032,13 +1033,15 @@ template <typename T, int N, int RO = 0> struct Engine {
       return hipErrorInvalidValue;
     }
   }
-  // 256 threads where a half plane's stages have at most 256 butterflies and
-  // it pays: 32^3 real FP32 274 -> 262 us, 64^3 real FP64 with 51 orbitals
-  // 5.12 -> 4.82 ms a whole exchange (64^3 FP32: 4.14 -> 4.22 ms)
+  // Threads, again by measurement size by size: 256 at 32^3 FP32 (real, whole
+  // exchange 274 -> 262 us) and at 64^3 FP64 (real, 51 orbitals 5.12 -> 4.82 ms);
+  // 64^3 FP32 was slower with 256 (4.14 -> 4.22 ms), 80^3 with 640 (15.29 ->
+  // 15.43); the other sizes were not varied.
   static constexpr int NT_HALF = (sizeof(T) == 4 && N == 32) || (sizeof(T) == 8 && N == 64)
                                      ? 256 : 512;
-  // waves per SIMD to budget registers for: two workgroups of 8 waves when
-  // two half planes fit the 160 KiB of LDS of a CU
+  // waves per SIMD to budget registers for: 4 when two half planes fit the 160
+  // KiB of LDS of a CU (two workgroups of 8 waves; of the 256-thread forms, 34
+  // KiB each at most, four of 4 waves), else 2
   static constexpr int W_HALF =
       (N / 2 * (N + 1) + N) * (int)sizeof(C<T>) * 2 <= 160 * 1024 ? 4 : 2;
   template <int SIGN, int SPLIT = 0, class Pro, class Epi>

@@ -714,22 +714,12 @@ static hipError_t enqueue_schedule(const lace_plan* p, const CellDev& c,
   return launch_schedule(d, st);
 }
 
-// Schedule, pair pipeline, energy reduction, W back to plane waves.
-// Requires the grid orbitals in the workspace.  Without profiling the host
-// launches the bound of the schedule's batch count (launch_bound) and the
-// kernels of batches past the schedule's end return at once, so nothing
-// waits on the host.  Consecutive batches alternate between two internal
-// streams when `overlap` (batch b on lane b % 2): a batch's passes A and B
-// overlap the previous batch's passes, and its pass C waits for the
-// previous pass C (they may share W grids), so W is summed in batch order
-// either way.  Profiled calls read the schedule back (they synchronize the
-// stream) and run the batches it holds one launch at a time on `st`.
-// Batches 0 .. nb - 1 of the workspace's table through the pair pipeline.
-// two: on two internal streams (batch b on lane b % 2), a batch's passes A
+// Batches 0 .. nb - 1 of the workspace's table through the pair pipeline, where
+// group_batches says so in groups on the caller's stream.
+// two: else on two internal streams (batch b on lane b % 2), a batch's passes A
 // and B overlapping the previous batch's pass C, the C passes in batch
-// order; the caller's stream waits for both lanes at the end.  Else all on
-// the caller's stream.
-// Where group_batches says so, in groups of batches on the caller's stream.
+// order; the caller's stream waits for both lanes at the end.  Not two: batch
+// by batch on the caller's stream.
 static hipError_t enqueue_batches(lace_plan* p, const CellDev& c, int n_orb,
                                   int64_t nb, int ppb, const Layout& L, void* ws,
                                   hipStream_t st, bool two) {
@@ -775,6 +765,14 @@ static hipError_t enqueue_batches(lace_plan* p, const CellDev& c, int n_orb,
   return e;
 }
 
+// Schedule, pair pipeline, energy reduction, W back to plane waves.
+// Requires the grid orbitals in the workspace.  Without profiling the host
+// launches the bound of the schedule's batch count (launch_bound) and the
+// kernels of batches past the schedule's end return at once, so nothing
+// waits on the host.  The two internal streams are used only when `overlap`;
+// W is summed in batch order either way (batches may share W grids).
+// Profiled calls read the schedule back (they synchronize the stream) and run
+// the batches it holds one launch at a time on `st`.
 static hipError_t enqueue_exchange(lace_plan* p, const CellDev& c, int n_orb,
                                    const PairSource& src, const Layout& L,
                                    void* ws, void* w_g, double* e_x,
