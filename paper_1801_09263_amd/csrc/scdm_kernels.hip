@@ -155,12 +155,12 @@ __device__ inline GridVec<G, VW> ldgrid(const G* p) {
 }
 
 // use(n, ld(n)) for n = n0, n0 + step, ... < n1, in that order, with U loads
-// issued before the first of them is used.  The order is pinned: left to
-// itself the compiler put each load of an unrolled loop right before its
-// use, one in flight at a time.  Whole call, so -> pinned: 24^3 with 450
-// complex FP64 orbitals 121 -> 49 ms, 300 real FP32 14.8 -> 11.9, 48^3 with
-// 200 complex FP32 19.7 -> 12.0, 64^3 with 64 real FP32 2.08 -> 1.90.  The
-// last round reads entry n1 - 1 in place of those past the end.
+// issued before the first of them is used, the rest in rounds of half as
+// many.  The order is pinned: left to itself the compiler put each load of an
+// unrolled loop right before its use, one in flight at a time.  Whole call, so
+// -> pinned: 24^3 with 450 complex FP64 orbitals 121 -> 46 ms, 300 real FP32 14.8
+// -> 10.0, 48^3 with 200 complex FP32 19.2 -> 10.3, 64^3 with 64 real FP32 2.05 ->
+// 1.77.
 template <int U, class Ld, class Use>
 __device__ __forceinline__ void in_flight(int n0, int n1, int step, Ld ld, Use use) {
   decltype(ld(0)) v[U];
@@ -172,18 +172,32 @@ __device__ __forceinline__ void in_flight(int n0, int n1, int step, Ld ld, Use u
 #pragma unroll
     for (int u = 0; u < U; ++u) use(n + u * step, v[u]);
   }
-  if (n >= n1) return;
+  if constexpr (U > 4) {
+    in_flight<U / 2>(n, n1, step, ld, use);
+  } else {
+    if (n >= n1) return;
 #pragma unroll
-  for (int u = 0; u < U; ++u) v[u] = ld(min(n + u * step, n1 - 1));
-  __builtin_amdgcn_sched_barrier(0);
+    for (int u = 0; u < U; ++u)
+      if (n + u * step < n1) v[u] = ld(n + u * step);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (n + u * step < n1) use(n + u * step, v[u]);
+    for (int u = 0; u < U; ++u)
+      if (n + u * step < n1) use(n + u * step, v[u]);
+  }
 }
+
+// Loads in flight per thread: two 16-byte ones on the grids that fill the chip,
+// where more only spread the accesses over more grids (16 / 4 / 2, whole call:
+// complex FP64 64^3 with 40 orbitals 2.02 / 1.79 / 1.74 ms, 120^3 with 7 557 / 556
+// / 546 us; one in flight costs 96^3 with 64 complex FP32 plane waves 8.08 for
+// 7.28 ms), sixteen on smaller ones, whose waves do not (16 / 8 / 4: 24^3 with
+// 450 complex FP64 46.2 / 49.3 / 55.5 ms, 48^3 with 200 complex FP32 within 3%).
+constexpr int VEC_U = 2;
+constexpr int SMALL_U = 16;
 
 // d(r) = sum_n |psi_n(r)|^2 (the diagonal of the density matrix), with
 // block-wise maxima of it; points <- 0, and missed <- 0 where given.
-template <typename G, int VW>
+template <typename G, int VW, int U>
 __global__ __launch_bounds__(AM_NT) void k_scdm_density(
     const G* psi, int n_orb, int64_t ng, double* d, uint16_t* missed,
     int32_t* points, double* pv, int64_t* pi) {
@@ -195,11 +209,11 @@ __global__ __launch_bounds__(AM_NT) void k_scdm_density(
     double s[VW];
 #pragma unroll
     for (int e = 0; e < VW; ++e) s[e] = 0.0;
-    in_flight<16>(0, n_orb, 1, [&](int n) { return ldgrid<G, VW>(psi + n * ng + r0); },
-                  [&](int, const GridVec<G, VW>& g) {
+    in_flight<U>(0, n_orb, 1, [&](int n) { return ldgrid<G, VW>(psi + n * ng + r0); },
+                 [&](int, const GridVec<G, VW>& g) {
 #pragma unroll
-                    for (int e = 0; e < VW; ++e) s[e] += norm_s(to_s(g.v[e], S{}));
-                  });
+                   for (int e = 0; e < VW; ++e) s[e] += norm_s(to_s(g.v[e], S{}));
+                 });
 #pragma unroll
     for (int e = 0; e < VW; ++e) {
       d[r0 + e] = s[e];
@@ -241,7 +255,7 @@ __device__ __forceinline__ void colsum(const S* A, int ld, int nx, int ny, const
     for (int e = 0; e < VS; ++e) sm[e] = zero_s(S{});
     const bool on = yv < nv && g < ngrp;
     if (on) {
-      in_flight<16>(g, nx, ngrp,
+      in_flight<NT == 256 ? 8 : 16>(g, nx, ngrp,
                     [&](int x) { return ldgrid<S, VS>(A + (int64_t)x * ld + yv * VS); },
                     [&](int x, const GridVec<S, VS>& a) {
                       const S vx = v[x];
@@ -335,7 +349,7 @@ __global__ __launch_bounds__(NT) void k_scdm_pick(
 // d(r) -= |q_k^H a_r|^2 = |sum_n q_kn psi_n(r)|^2 for every point not yet
 // taken, with the next pick's block-wise argmax.  A thread takes VW
 // consecutive points, one 16-byte load per orbital.  q: q_k in LDS.
-template <typename G, int VW>
+template <typename G, int VW, int U>
 __device__ __forceinline__ ArgMax downdate_all(const G* psi, int n_orb, int64_t ng,
                                const typename Scal<G>::S* q, double* d) {
   using S = typename Scal<G>::S;
@@ -346,12 +360,12 @@ __device__ __forceinline__ ArgMax downdate_all(const G* psi, int n_orb, int64_t 
     S s[VW];
 #pragma unroll
     for (int e = 0; e < VW; ++e) s[e] = zero_s(S{});
-    in_flight<16>(0, n_orb, 1, [&](int n) { return ldgrid<G, VW>(psi + n * ng + r0); },
-                  [&](int n, const GridVec<G, VW>& g) {
-                    const S qn = q[n];
+    in_flight<U>(0, n_orb, 1, [&](int n) { return ldgrid<G, VW>(psi + n * ng + r0); },
+                 [&](int n, const GridVec<G, VW>& g) {
+                   const S qn = q[n];
 #pragma unroll
-                    for (int e = 0; e < VW; ++e) s[e] = mad(qn, to_s(g.v[e], S{}), s[e]);
-                  });
+                   for (int e = 0; e < VW; ++e) s[e] = mad(qn, to_s(g.v[e], S{}), s[e]);
+                 });
 #pragma unroll
     for (int e = 0; e < VW; ++e) {
       const double old = d[r0 + e];
@@ -366,7 +380,7 @@ __device__ __forceinline__ ArgMax downdate_all(const G* psi, int n_orb, int64_t 
   return m;
 }
 
-template <typename G, int VW>
+template <typename G, int VW, int U>
 __global__ __launch_bounds__(AM_NT) void k_scdm_downdate(
     const G* psi, int n_orb, int64_t ng, const typename Scal<G>::S* Q, int k,
     double* d, double* pv, int64_t* pi) {
@@ -375,7 +389,7 @@ __global__ __launch_bounds__(AM_NT) void k_scdm_downdate(
   S* qs = reinterpret_cast<S*>(lds);
   for (int n = threadIdx.x; n < n_orb; n += AM_NT) qs[n] = Q[(int64_t)k * q_ld<S>(n_orb) + n];
   __syncthreads();
-  const ArgMax m = block_argmax<AM_NT>(downdate_all<G, VW>(psi, n_orb, ng, qs, d));
+  const ArgMax m = block_argmax<AM_NT>(downdate_all<G, VW, U>(psi, n_orb, ng, qs, d));
   if (threadIdx.x == 0) {
     pv[blockIdx.x] = m.v;
     pi[blockIdx.x] = m.i;
@@ -784,7 +798,7 @@ __global__ __launch_bounds__(AM_NT) void k_lazy_downdate(
   if (c->full) {
     for (int n = tid; n < n_orb; n += AM_NT) qs[n] = Q[(int64_t)k * q_ld<S>(n_orb) + n];
     __syncthreads();
-    m = downdate_all<G, VW>(psi, n_orb, ng, qs, d);
+    m = downdate_all<G, VW, VEC_U>(psi, n_orb, ng, qs, d);
   } else if (blockIdx.x * LZ_PTS < (unsigned)c->count) {
     // 64 points a workgroup, a quarter of the orbitals a wave
     __shared__ S part[AM_NT / 64][64];
@@ -899,10 +913,10 @@ static hipError_t scdm_t(const G* psi, int n_orb, int64_t ng, double* d,
   b += up256(4 * (size_t)cap);
   G* cols = reinterpret_cast<G*>(b);
   if (vec)
-    LACE_LAUNCH((k_scdm_density<G, VW>), dim3(parts), dim3(AM_NT), 0, st, psi,
+    LACE_LAUNCH((k_scdm_density<G, VW, VEC_U>), dim3(parts), dim3(AM_NT), 0, st, psi,
                 n_orb, ng, d, missed, points, pv, pi);
   else
-    LACE_LAUNCH((k_scdm_density<G, 1>), dim3(parts), dim3(AM_NT), 0, st, psi,
+    LACE_LAUNCH((k_scdm_density<G, 1, SMALL_U>), dim3(parts), dim3(AM_NT), 0, st, psi,
                 n_orb, ng, d, missed, points, pv, pi);
   hipError_t e = hipGetLastError();
   // Threads of the pick: Gram-Schmidt against many directions is bound by how
@@ -958,10 +972,10 @@ static hipError_t scdm_t(const G* psi, int n_orb, int64_t ng, double* d,
       if ((e = eager_pick(k)) != hipSuccess) return e;
       if (k + 1 < n_orb) {
         if (vec)
-          LACE_LAUNCH((k_scdm_downdate<G, VW>), dim3(parts), dim3(AM_NT), qlds, st,
+          LACE_LAUNCH((k_scdm_downdate<G, VW, VEC_U>), dim3(parts), dim3(AM_NT), qlds, st,
                       psi, n_orb, ng, Q, k, d, pv, pi);
         else
-          LACE_LAUNCH((k_scdm_downdate<G, 1>), dim3(parts), dim3(AM_NT), qlds, st,
+          LACE_LAUNCH((k_scdm_downdate<G, 1, SMALL_U>), dim3(parts), dim3(AM_NT), qlds, st,
                       psi, n_orb, ng, Q, k, d, pv, pi);
       }
       e = hipGetLastError();
