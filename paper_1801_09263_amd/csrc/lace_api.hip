@@ -613,8 +613,10 @@ static int batch_slots(const lace_plan* p, int n_orb, int ppb) {
 //                3.08 -> 3.04, 96^3 / 128 (113 MB) 25.8 -> 24.4; beyond 80^3 /
 //                96 (131 MB) 14.4 -> 15.3, 120^3 / 256 (221 MB) 317 -> 328
 //   complex FP32 24^3 / 64 (7 MB) 2.39 -> 1.93, 64^3 / 80 (67 MB) 15.6 -> 14.7,
-//                80^3 / 22 (90 MB) 2.52 -> 2.51, 96^3 / 16 (113 MB) 2.26 -> 2.25,
-//                120^3 / 8 (110 MB) 1.49 -> 1.50
+//                120 33.3 -> 34.1, 180 79.9 -> 78.1, 80^3 / 22 (90 MB) 2.52 -> 2.51,
+//                96^3 / 16 (113 MB) 2.26 -> 2.25, 120^3 / 8 (110 MB) 1.49 -> 1.50;
+//                48^3 with 32 pairs (28 MB) / 40 2.06 -> 1.93, but / 64 4.12 -> 4.32
+//                and / 160 24.5 -> 25.1 with whole planes, 26.6 -> 25.5 with half ones
 //   FP64         complex 48^3 / 16 (28 MB) 749 -> 678 us, / 24 (42 MB) 1427 ->
 //                1511, real 48^3 / 36 (32 MB) 1.54 -> 1.38 ms
 // A group of two batches (complex: of three as well) of more than 32 MB joins
